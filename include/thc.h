@@ -212,7 +212,7 @@ int thc_mp2_density(thc_ctx* ctx, const double* Z, double* Doo, double* Dvv);
  *   objective  HOST [sweeps + 1] out: O before the first sweep and after each (NULL: not computed)
  *   cg_iters   HOST out: the most CG iterations one solve took (may be NULL)
  * Work on `stream`; synchronizes it before returning.  Allocates and frees its own workspace
- * (about (IJ + 3 max(I, J, K) + 7 n) n doubles): it is a set-up step, not part of an iteration.
+ * (about (IJ + 8 max(I, J, K) + 5 n) n doubles and 70 MB of K slices): it is a set-up step, not part of an iteration.
  * Returns THC_ENOTCONV if some solve reached cg_maxit (the factors are then still updated with the
  * last iterate), THC_EINVAL for bad sizes, THC_ENOMEM, THC_EDEVICE. */
 int thc_cp_als(const double* A, int64_t I, int64_t J, int64_t K, int64_t n, const double* w1, const double* w2,

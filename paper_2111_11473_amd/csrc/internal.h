@@ -77,8 +77,12 @@ hipError_t k_diag(int64_t P, const double* X, int64_t ldx, double* d, hipStream_
 hipError_t k_trace_sq(int64_t nb, int64_t o, const double* K, double* out, hipStream_t s);
 hipError_t k_diag_eri(int64_t P, int64_t Q, int64_t o, const double* xo, const double* Rx, double* Cx,
                       hipStream_t s);
-hipError_t k_dot(int64_t n, const double* x, const double* y, double* out, hipStream_t s);
-hipError_t k_sum(int64_t n, const double* x, double* out, hipStream_t s);
+// parts: scratch of DOT_PARTS doubles (long sums run as DOT_PARTS blocks and one that adds them up).
+constexpr int DOT_PARTS = 256;
+hipError_t k_dot(int64_t n, const double* x, const double* y, double* out, double* parts, hipStream_t s);
+hipError_t k_sum(int64_t n, const double* x, double* out, double* parts, hipStream_t s);
+// out[k] = sum_e x_k[e] y[e] for m <= 16 vectors x_k at once; parts: m DOT_PARTS doubles
+hipError_t k_dots(int64_t n, int m, const double* const* xs, const double* y, double* out, double* parts, hipStream_t s);
 hipError_t k_jacobi(int64_t P, int64_t o, int64_t v, const double* sh, const double* e, const double* delta, const double* s1,
                     const double* eps, double* Th, double* t1, double* dT, double* dt1, hipStream_t s);
 hipError_t k_guess_features(int64_t P, int64_t o, int64_t v, const double* Th, const double* e, const double* eps,
@@ -112,12 +116,20 @@ hipError_t cp_mttkrp_reduce(int64_t I, int64_t J, int64_t n, const double* T, co
 int64_t cp_wnorm2_parts(int64_t I, int64_t J, int64_t K);
 hipError_t cp_wnorm2(int64_t I, int64_t J, int64_t K, const double* A, const double* w1, const double* w2,
                      const double* w3, double* part, hipStream_t s);
-hipError_t cp_col_dot(int64_t n, int64_t m, const double* A, const double* B, double* out, hipStream_t s);
+// Passes of one block-CG iteration (see cpals.hip): partials are [cp_cg_splits(n)][m]; SU, SP are ns
+// slices of n x m; flag[0] = 0 makes a pass do nothing, cp_cg_dir sets flag[1] while a column has not
+// converged; cp_cg_flags starts a batch (flag[0] = 1, the others 0).
+int cp_cg_splits(int64_t n);
+hipError_t cp_cg_start(int64_t n, int64_t m, int ns, const double* SU, const double* B, const double* d, double* R,
+                       double* P, double* rz, double* bb, hipStream_t s);
+hipError_t cp_cg_pq(int64_t n, int64_t m, int ns, const double* SP, const double* P, double* Q, double* pq,
+                    const int* flag, hipStream_t s);
 hipError_t cp_cg_step(int64_t n, int64_t m, const double* rz, const double* pq, const double* P, const double* Q,
-                      double* U, double* R, hipStream_t s);
-hipError_t cp_cg_precond(int64_t n, int64_t m, const double* d, const double* R, double* Zr, hipStream_t s);
-hipError_t cp_cg_dir(int64_t n, int64_t m, const double* rz_new, const double* rz_old, const double* Zr, double* P,
-                     hipStream_t s);
+                      const double* d, double* U, double* R, double* rr, double* rz_new, const int* flag,
+                      hipStream_t s);
+hipError_t cp_cg_dir(int64_t n, int64_t m, double tol, const double* rz_new, const double* rz_old, const double* rr,
+                     const double* bb, const double* R, const double* d, double* P, int* flag, hipStream_t s);
+hipError_t cp_cg_flags(int count, int* flag, hipStream_t s);
 hipError_t cp_diag(int64_t n, const double* S, double* d, hipStream_t s);
 
 // Fused exchange contraction Gt^X = xo (z o (xo^T Rx^X))^T for X = 0..nx-1 (kernels_exch.hip);

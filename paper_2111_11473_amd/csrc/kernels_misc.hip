@@ -218,12 +218,25 @@ __global__ void diag_eri_kernel(int64_t P, int64_t Q, int64_t o, const double* _
   }
 }
 
-__global__ void dot_kernel(int64_t n, const double* __restrict__ x, const double* __restrict__ y,
-                           double* __restrict__ out) {
+// Vectors of a set of dot products with one common factor.
+struct DotSet {
+  const double* x[16];
+};
+// One block per vector (blockIdx.y) and part (blockIdx.x): out[vector * gridDim.x + part] = the sum of
+// x_k y over that part's elements.  One block of 1024 threads streamed 10^6 elements in 210 us (36
+// GB/s); DOT_PARTS blocks take 6 us and the block that adds their sums 2 us.
+__global__ __launch_bounds__(1024) void dot_kernel(int64_t n, DotSet xs, const double* __restrict__ y,
+                                                   double* __restrict__ out) {
+  const double* __restrict__ x = xs.x[blockIdx.y];
   double s = 0.0;
-  for (int64_t e = threadIdx.x; e < n; e += blockDim.x) s += x[e] * (y ? y[e] : 1.0);
+  for (int64_t e = (int64_t)blockIdx.x * 1024 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 1024)
+    s += x[e] * (y ? y[e] : 1.0);
   s = block_sum<1024>(s);
-  if (threadIdx.x == 0) out[0] = s;
+  if (threadIdx.x == 0) out[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+}
+__global__ __launch_bounds__(DOT_PARTS) void dot_parts_kernel(const double* __restrict__ parts, double* __restrict__ out) {
+  const double s = block_sum<DOT_PARTS>(parts[(int64_t)blockIdx.x * DOT_PARTS + threadIdx.x]);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 __global__ void jacobi_kernel(int64_t P, int64_t o, int64_t v, const double* __restrict__ sh,
@@ -396,11 +409,20 @@ hipError_t k_diag_eri(int64_t P, int64_t Q, int64_t o, const double* xo, const d
                       hipStream_t s) {
   LAUNCH(diag_eri_kernel, dim3(nblocks(P * Q)), dim3(TPB), P, Q, o, xo, Rx, Cx);
 }
-hipError_t k_dot(int64_t n, const double* x, const double* y, double* out, hipStream_t s) {
-  LAUNCH(dot_kernel, dim3(1), dim3(1024), n, x, y, out);
+// Up to 16384 elements (16 a thread) one block is as fast as the two launches of the parted sum.
+hipError_t k_dots(int64_t n, int m, const double* const* xs, const double* y, double* out, double* parts, hipStream_t s) {
+  if (m < 1 || m > 16) return m < 1 ? hipSuccess : hipErrorInvalidValue;
+  DotSet d{};
+  for (int k = 0; k < m; ++k) d.x[k] = xs[k];
+  if (n <= 16384) LAUNCH(dot_kernel, dim3(1, (unsigned)m), dim3(1024), n, d, y, out);
+  hipLaunchKernelGGL(dot_kernel, dim3(DOT_PARTS, (unsigned)m), dim3(1024), 0, s, n, d, y, parts);
+  LAUNCH(dot_parts_kernel, dim3((unsigned)m), dim3(DOT_PARTS), parts, out);
 }
-hipError_t k_sum(int64_t n, const double* x, double* out, hipStream_t s) {
-  LAUNCH(dot_kernel, dim3(1), dim3(1024), n, x, (const double*)nullptr, out);
+hipError_t k_dot(int64_t n, const double* x, const double* y, double* out, double* parts, hipStream_t s) {
+  return k_dots(n, 1, &x, y, out, parts, s);
+}
+hipError_t k_sum(int64_t n, const double* x, double* out, double* parts, hipStream_t s) {
+  return k_dots(n, 1, &x, nullptr, out, parts, s);
 }
 hipError_t k_jacobi(int64_t P, int64_t o, int64_t v, const double* sh, const double* e, const double* delta, const double* s1,
                     const double* eps, double* Th, double* t1, double* dT, double* dt1, hipStream_t s) {

@@ -945,10 +945,10 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
   RCHK(progress(ctx, "fused Cholesky pass done, vectors", nL, nL));
   // energy partial sums: scal[0] = sum_A Atil^T T Atil, scal[1] = exchange, scal[2] = sum d_A^2,
   // scal[3] = sum tr(K_A^2)
-  MISC(k_sum(nL, ctx->ej, ctx->scal + 0, s));
-  MISC(k_sum(nL * 64, ctx->ek, ctx->scal + 1, s));
-  MISC(k_dot(nL, ctx->dvecA, ctx->dvecA, ctx->scal + 2, s));
-  MISC(k_sum(nL, ctx->trK, ctx->scal + 3, s));
+  MISC(k_sum(nL, ctx->ej, ctx->scal + 0, ctx->gws, s));
+  MISC(k_sum(nL * 64, ctx->ek, ctx->scal + 1, ctx->gws, s));
+  MISC(k_dot(nL, ctx->dvecA, ctx->dvecA, ctx->scal + 2, ctx->gws, s));
+  MISC(k_sum(nL, ctx->trK, ctx->scal + 3, ctx->gws, s));
 
   // ---------------- Fock matrix, T1-transformed (Eq. 24-27) -----------------------------------
   ctx->section = "gemm@fock";
@@ -1198,8 +1198,8 @@ int project_basis(thc_ctx* ctx) {
   const int64_t P = ctx->P;
   RCHK(gemm(ctx, mk(P, P, P, ctx->sig, P, false, ctx->W, P, false, ctx->Qm, P)));
   RCHK(gemm(ctx, mk(P, P, P, ctx->W, P, true, ctx->Qm, P, false, ctx->sigh, P)));
-  MISC(k_dot(P * P, ctx->sigh, ctx->sigh, ctx->scal + 8, ctx->stream));
-  MISC(k_dot(ctx->ov, ctx->sig1, ctx->sig1, ctx->scal + 9, ctx->stream));
+  MISC(k_dot(P * P, ctx->sigh, ctx->sigh, ctx->scal + 8, ctx->gws, ctx->stream));
+  MISC(k_dot(ctx->ov, ctx->sig1, ctx->sig1, ctx->scal + 9, ctx->gws, ctx->stream));
   return THC_OK;
 }
 
@@ -1487,7 +1487,7 @@ int generate_inputs(thc_ctx* ctx) {
       rc = h2d(ctx, x, ones.data(), nL * sizeof(double));
     }
     for (int it = 0; it < 200 && rc == THC_OK; ++it) {
-      if (k_gemv(nL, nL, G, nL, x, y, s) != hipSuccess || k_dot(nL, y, y, ctx->scal + 60, s) != hipSuccess ||
+      if (k_gemv(nL, nL, G, nL, x, y, s) != hipSuccess || k_dot(nL, y, y, ctx->scal + 60, ctx->gws, s) != hipSuccess ||
           synth_normalize(nL, y, ctx->scal + 60, x, s) != hipSuccess) {
         ctx->err = "gamma rule: kernel launch failed";
         rc = THC_EDEVICE;
@@ -1929,7 +1929,7 @@ int thc_iterate(thc_ctx* ctx, double tol, int maxit, int* iters, double* rnorm) 
     }
     float* phi = (float*)ctx->dT;  // the Jacobi step's buffer is free before the first residual
     float* pred = phi + P * 10;
-    MISC(k_dot(PP, ctx->Th, ctx->Th, ctx->scal + 40, s));
+    MISC(k_dot(PP, ctx->Th, ctx->Th, ctx->scal + 40, ctx->gws, s));
     MISC(k_guess_features(P, ctx->o, ctx->v, ctx->Th, ctx->e, ctx->eps, ctx->scal + 40, phi, s));
     if (hipStreamSynchronize(net->stream) != hipSuccess) return THC_EDEVICE;  // its parameters are final
     if (!net->packed) {
@@ -2036,8 +2036,9 @@ int thc_iterate(thc_ctx* ctx, double tol, int maxit, int* iters, double* rnorm) 
       // inner products of the new error with every stored error (device), B on the host
       std::vector<int> slots(mfull);
       for (int k = 0; k < mfull; ++k) slots[k] = (ctx->diis_head - mfull + k + 2 * dm) % dm;  // oldest first
-      for (int k = 0; k < mfull; ++k)
-        MISC(k_dot(len, ctx->derr + (int64_t)slots[k] * len, es, ctx->scal + 16 + k, s));
+      const double* stored[16];
+      for (int k = 0; k < mfull; ++k) stored[k] = ctx->derr + (int64_t)slots[k] * len;
+      MISC(k_dots(len, mfull, stored, es, ctx->scal + 16, ctx->gws, s));
       double bd[16];
       RCHK(d2h(ctx, bd, ctx->scal + 16, mfull * sizeof(double)));
       for (int k = 0; k < mfull; ++k) {
@@ -2188,53 +2189,78 @@ int thc_profile_flops(const thc_ctx* ctx, double* fp64_flops, double* fp32_flops
 // ------------------------------------------------------------------------------------------
 // Weighted CP-ALS (Sec. II.c-d, Eq. 15-16, 21; Appendix I, Eq. 43-46).
 namespace {
-struct CpWork {
-  std::vector<void*> mem;
-  ~CpWork() { for (void* q : mem) (void)hipFree(q); }
-  double* get(size_t n) {
-    void* q = nullptr;
-    if (hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(double)) != hipSuccess) return nullptr;
-    mem.push_back(q);
-    return (double*)q;
-  }
-};
-
 #define CPCHK(expr)                        \
   do {                                     \
     if ((expr) != hipSuccess) return THC_EDEVICE; \
   } while (0)
 
+// Device workspace of one call: pieces of one allocation (25 allocations and frees took 1 ms a call).
+struct CpWork {
+  void* mem = nullptr;
+  std::vector<std::pair<double**, size_t>> want;
+  ~CpWork() { if (mem) (void)hipFree(mem); }
+  void add(double** p, size_t n) { want.push_back({p, aligned(n)}); }
+  bool alloc() {
+    size_t total = 0;
+    for (const auto& w : want) total += w.second;
+    if (hipMalloc(&mem, total * sizeof(double)) != hipSuccess) {
+      (void)hipGetLastError();
+      mem = nullptr;
+      return false;
+    }
+    double* at = (double*)mem;
+    for (const auto& w : want) { *w.first = at; at += w.second; }
+    return true;
+  }
+};
+
+// K slices of the product S P (n x m, K = n): about three 64 x 64 tiles a CU, at least 128 deep, as
+// gemm_f64's own split; the slices are added by the CG pass that reads them.
+int cp_slices(int64_t n, int64_t m) {
+  const int64_t t64 = ((n + 63) / 64) * ((m + 63) / 64);
+  if (n < 256 || t64 >= 384) return 1;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(n / 128, (768 + t64 - 1) / t64), 32));
+}
+
+constexpr int CG_BATCH = 6;  // iterations between two looks of the host at the flags
+
+struct CgBufs {
+  double *d, *R, *P, *Q, *slices, *rz[2], *pq, *rr, *bb;
+  int* flag;  // CG_BATCH + 1
+};
+
 // Solves S U = B ([n][m], column c one right-hand side) by conjugate gradients preconditioned with
 // diag(S), from the U given; stops when every column's residual is below tol times its right-hand
 // side.  *iters: iterations taken; returns THC_ENOTCONV if maxit is reached first.
-int cp_pcg(int64_t n, int64_t m, const double* S, const double* B, double* U, double tol, int maxit, double* d,
-           double* R, double* Zr, double* P, double* Q, double* rz, double* rz2, double* pq, double* rr, double* bb,
+int cp_pcg(int64_t n, int64_t m, const double* S, const double* B, double* U, double tol, int maxit, const CgBufs& w,
            int* iters, hipStream_t s) {
-  CPCHK(cp_diag(n, S, d, s));
-  CPCHK(hipMemcpyAsync(R, B, n * m * sizeof(double), hipMemcpyDeviceToDevice, s));
-  CPCHK(gemm_f64(mk(n, m, n, S, n, false, U, m, false, R, m, -1.0, 1.0), s));
-  CPCHK(cp_cg_precond(n, m, d, R, Zr, s));
-  CPCHK(hipMemcpyAsync(P, Zr, n * m * sizeof(double), hipMemcpyDeviceToDevice, s));
-  CPCHK(cp_col_dot(n, m, R, Zr, rz, s));
-  CPCHK(cp_col_dot(n, m, B, B, bb, s));
-  std::vector<double> hr(m), hb(m);
-  CPCHK(hipMemcpyAsync(hb.data(), bb, m * sizeof(double), hipMemcpyDeviceToHost, s));
-  CPCHK(hipStreamSynchronize(s));
-  for (int it = 1; it <= maxit; ++it) {
-    CPCHK(gemm_f64(mk(n, m, n, S, n, false, P, m, false, Q, m), s));
-    CPCHK(cp_col_dot(n, m, P, Q, pq, s));
-    CPCHK(cp_cg_step(n, m, rz, pq, P, Q, U, R, s));
-    CPCHK(cp_col_dot(n, m, R, R, rr, s));
-    CPCHK(hipMemcpyAsync(hr.data(), rr, m * sizeof(double), hipMemcpyDeviceToHost, s));
+  const int ns = cp_slices(n, m);
+  auto times_S = [&](const double* X) {
+    Gemm g = mk(n, m, n, S, n, false, X, m, false, w.slices, m);
+    g.ksplit = ns;
+    g.sSplit = n * m;
+    return gemm_f64(g, s);
+  };
+  CPCHK(cp_diag(n, S, w.d, s));
+  CPCHK(times_S(U));
+  CPCHK(cp_cg_start(n, m, ns, w.slices, B, w.d, w.R, w.P, w.rz[0], w.bb, s));
+  int it = 0, cur = 0;
+  while (it < maxit) {
+    const int nb = std::min(CG_BATCH, maxit - it);
+    CPCHK(cp_cg_flags(nb + 1, w.flag, s));
+    for (int k = 0; k < nb; ++k) {
+      CPCHK(times_S(w.P));
+      CPCHK(cp_cg_pq(n, m, ns, w.slices, w.P, w.Q, w.pq, w.flag + k, s));
+      CPCHK(cp_cg_step(n, m, w.rz[cur], w.pq, w.P, w.Q, w.d, U, w.R, w.rr, w.rz[cur ^ 1], w.flag + k, s));
+      CPCHK(cp_cg_dir(n, m, tol, w.rz[cur ^ 1], w.rz[cur], w.rr, w.bb, w.R, w.d, w.P, w.flag + k, s));
+      cur ^= 1;
+    }
+    int flag[CG_BATCH + 1];
+    CPCHK(hipMemcpyAsync(flag, w.flag, (nb + 1) * sizeof(int), hipMemcpyDeviceToHost, s));
     CPCHK(hipStreamSynchronize(s));
-    bool done = true;
-    for (int64_t c = 0; c < m && done; ++c) done = std::sqrt(hr[c]) <= tol * std::sqrt(hb[c]);
+    for (int k = 0; k < nb; ++k) it += flag[k];
     *iters = it;
-    if (done) return THC_OK;
-    CPCHK(cp_cg_precond(n, m, d, R, Zr, s));
-    CPCHK(cp_col_dot(n, m, R, Zr, rz2, s));
-    CPCHK(cp_cg_dir(n, m, rz2, rz, Zr, P, s));
-    std::swap(rz, rz2);
+    if (!flag[nb]) return THC_OK;
   }
   return THC_ENOTCONV;
 }
@@ -2247,23 +2273,32 @@ int thc_cp_als(const double* A, int64_t I, int64_t J, int64_t K, int64_t n, cons
     return THC_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const int64_t m = std::max(std::max(I, J), K), IJ = I * J;
+  const int64_t nparts = cp_wnorm2_parts(I, J, K), splits = cp_cg_splits(n);
+  int64_t slices = 0;
+  for (int64_t c : {I, J, K}) slices = std::max(slices, cp_slices(n, c) * n * c);
   CpWork w;
-  double *TB = w.get(IJ * n), *Xw = w.get(I * n), *Yw = w.get(J * n), *Zw = w.get(K * n), *Zwt = w.get(K * n);
-  double *G1 = w.get(n * n), *G2 = w.get(n * n), *G3 = w.get(n * n), *S = w.get(n * n), *H = w.get(n * n);
-  double *Bt = w.get(n * m), *U = w.get(n * m), *R = w.get(n * m), *Zr = w.get(n * m), *P = w.get(n * m),
-         *Qb = w.get(n * m);
-  double *d = w.get(n), *rz = w.get(m), *rz2 = w.get(m), *pq = w.get(m), *rr = w.get(m), *bb = w.get(m);
-  const int64_t nparts = cp_wnorm2_parts(I, J, K);
-  double *parts = w.get(nparts), *sc = w.get(4);
-  if (!TB || !Xw || !Yw || !Zw || !Zwt || !G1 || !G2 || !G3 || !S || !H || !Bt || !U || !R || !Zr || !P || !Qb || !d ||
-      !rz || !rz2 || !pq || !rr || !bb || !parts || !sc)
-    return THC_ENOMEM;
+  double *TB, *Xw, *Yw, *Zw, *Zwt, *G1, *G2, *G3, *S, *H, *Bt, *U, *parts, *dots, *sc, *flag, *gws;
+  CgBufs cg;
+  w.add(&TB, IJ * n); w.add(&Xw, I * n); w.add(&Yw, J * n); w.add(&Zw, K * n); w.add(&Zwt, K * n);
+  for (double** g : {&G1, &G2, &G3, &S, &H}) w.add(g, n * n);
+  for (double** g : {&Bt, &U, &cg.R, &cg.P, &cg.Q}) w.add(g, n * m);
+  w.add(&cg.slices, slices); w.add(&cg.d, n);
+  for (double** g : {&cg.rz[0], &cg.rz[1], &cg.pq, &cg.rr, &cg.bb}) w.add(g, splits * m);
+  w.add(&parts, nparts); w.add(&dots, DOT_PARTS); w.add(&sc, 4); w.add(&flag, CG_BATCH + 1); w.add(&gws, GEMM_WS);
+  if (!w.alloc()) return THC_ENOMEM;
+  cg.flag = (int*)flag;
+  // a product, its K split over the workspace when it has few output tiles
+  auto product = [&](Gemm g) {
+    g.ws = gws;
+    g.ws_len = GEMM_WS;
+    return gemm_f64(g, s);
+  };
   int worst = 0, rc_all = THC_OK;
   // one factor update: S U = B with U = F^T warm-started from F, then F = U^T
   auto solve = [&](double* F, int64_t rows) -> int {
     CPCHK(k_copy2d(1, n, rows, F, n, 0, U, rows, 0, true, s));
     int its = 0;
-    const int rc = cp_pcg(n, rows, S, Bt, U, cg_tol, cg_maxit, d, R, Zr, P, Qb, rz, rz2, pq, rr, bb, &its, s);
+    const int rc = cp_pcg(n, rows, S, Bt, U, cg_tol, cg_maxit, cg, &its, s);
     worst = std::max(worst, its);
     if (rc == THC_ENOTCONV) rc_all = THC_ENOTCONV;
     else if (rc != THC_OK) return rc;
@@ -2272,58 +2307,64 @@ int thc_cp_als(const double* A, int64_t I, int64_t J, int64_t K, int64_t n, cons
   };
   // objective = |A_w|^2 - 2 sum_kn w3_k^2 Z_kn R_Z[k][n] + sum (G1 o G2 o G3), all with the current factors
   double anorm = 0.0;
-  {
+  if (objective) {
     CPCHK(cp_wnorm2(I, J, K, A, w1, w2, w3, parts, s));
-    CPCHK(k_sum(nparts, parts, sc, s));
+    CPCHK(k_sum(nparts, parts, sc, dots, s));
     CPCHK(hipMemcpyAsync(&anorm, sc, sizeof(double), hipMemcpyDeviceToHost, s));
     CPCHK(hipStreamSynchronize(s));
   }
-  auto grams = [&]() -> int {  // Xw, Yw, Zw and G1 = X^T Xw, G2 = Y^T Yw, G3 = Z^T Zw
-    CPCHK(cp_weighted_rows(I, n, w1, X, Xw, s));
-    CPCHK(cp_weighted_rows(J, n, w2, Y, Yw, s));
-    CPCHK(cp_weighted_rows(K, n, w3, Z, Zw, s));
-    CPCHK(gemm_f64(mk(n, n, I, X, n, true, Xw, n, false, G1, n), s));
-    CPCHK(gemm_f64(mk(n, n, J, Y, n, true, Yw, n, false, G2, n), s));
-    CPCHK(gemm_f64(mk(n, n, K, Z, n, true, Zw, n, false, G3, n), s));
+  // the weighted factor and the Gram matrix of one index
+  auto gram = [&](int64_t rows, const double* wt, const double* F, double* Fw, double* G) -> int {
+    CPCHK(cp_weighted_rows(rows, n, wt, F, Fw, s));
+    CPCHK(product(mk(n, n, rows, F, n, true, Fw, n, false, G, n)));
     return THC_OK;
   };
-  auto record = [&](int idx) -> int {  // objective of the current factors into objective[idx]
-    if (!objective) return THC_OK;
-    RCHK(grams());
-    // R_Z^T = KR(Xw, Yw)^T A  ([n][K])
+  // R_Z^T = KR(Xw, Yw)^T A ([n][K]) into Bt
+  auto rhs_z = [&]() -> int {
     CPCHK(k_kr(I, J, n, Xw, Yw, TB, s));
-    CPCHK(gemm_f64(mk(n, K, IJ, TB, n, true, A, K, false, Bt, K), s));
+    CPCHK(product(mk(n, K, IJ, TB, n, true, A, K, false, Bt, K)));
+    return THC_OK;
+  };
+  // objective of the current factors into objective[idx]; Bt holds R_Z^T of the current X and Y and the
+  // weighted factors and Gram matrices are those of the current factors
+  auto record = [&](int idx) -> int {
+    if (!objective) return THC_OK;
     CPCHK(k_copy2d(1, n, K, Zw, n, 0, Zwt, K, 0, true, s));
-    CPCHK(k_dot(n * K, Zwt, Bt, sc, s));
+    CPCHK(k_dot(n * K, Zwt, Bt, sc, dots, s));
     CPCHK(k_hadamard(n * n, G1, G2, 1.0, 0.0, H, s));
-    CPCHK(k_dot(n * n, H, G3, sc + 1, s));
+    CPCHK(k_dot(n * n, H, G3, sc + 1, dots, s));
     double h[2];
     CPCHK(hipMemcpyAsync(h, sc, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     CPCHK(hipStreamSynchronize(s));
     objective[idx] = anorm - 2.0 * h[0] + h[1];
     return THC_OK;
   };
-  RCHK(record(0));
+  if (sweeps > 0 || objective) {
+    RCHK(gram(I, w1, X, Xw, G1));
+    RCHK(gram(J, w2, Y, Yw, G2));
+    RCHK(gram(K, w3, Z, Zw, G3));
+  }
+  if (objective) {
+    RCHK(rhs_z());
+    RCHK(record(0));
+  }
   for (int sw = 0; sw < sweeps; ++sw) {
-    RCHK(grams());
     // X: T = A (W3^2 Z) (IJ x n); B_X^T[n][i] = sum_j w2_j^2 Y_jn T[i][j][n]; S = G2 o G3
-    CPCHK(gemm_f64(mk(IJ, n, K, A, K, false, Zw, n, false, TB, n), s));
+    CPCHK(product(mk(IJ, n, K, A, K, false, Zw, n, false, TB, n)));
     CPCHK(cp_mttkrp_reduce(I, J, n, TB, Yw, true, Bt, s));
     CPCHK(k_hadamard(n * n, G2, G3, 1.0, 0.0, S, s));
     RCHK(solve(X, I));
     // Y: B_Y^T[n][j] = sum_i w1_i^2 X_in T[i][j][n] (T unchanged: it depends on Z only); S = G1 o G3
-    CPCHK(cp_weighted_rows(I, n, w1, X, Xw, s));
-    CPCHK(gemm_f64(mk(n, n, I, X, n, true, Xw, n, false, G1, n), s));
+    RCHK(gram(I, w1, X, Xw, G1));
     CPCHK(cp_mttkrp_reduce(I, J, n, TB, Xw, false, Bt, s));
     CPCHK(k_hadamard(n * n, G1, G3, 1.0, 0.0, S, s));
     RCHK(solve(Y, J));
-    // Z: B_Z^T = KR(W1^2 X, W2^2 Y)^T A ([n][K]); S = G1 o G2
-    CPCHK(cp_weighted_rows(J, n, w2, Y, Yw, s));
-    CPCHK(gemm_f64(mk(n, n, J, Y, n, true, Yw, n, false, G2, n), s));
-    CPCHK(k_kr(I, J, n, Xw, Yw, TB, s));
-    CPCHK(gemm_f64(mk(n, K, IJ, TB, n, true, A, K, false, Bt, K), s));
+    // Z: B_Z^T = KR(W1^2 X, W2^2 Y)^T A; S = G1 o G2
+    RCHK(gram(J, w2, Y, Yw, G2));
+    RCHK(rhs_z());
     CPCHK(k_hadamard(n * n, G1, G2, 1.0, 0.0, S, s));
     RCHK(solve(Z, K));
+    RCHK(gram(K, w3, Z, Zw, G3));
     RCHK(record(sw + 1));
   }
   CPCHK(hipStreamSynchronize(s));
@@ -2351,7 +2392,7 @@ int thc_dgemm(int transA, int transB, int64_t M, int64_t N, int64_t K, double al
 int thc_guess_features(thc_ctx* ctx, float* phi) {
   if (!ctx || !phi) return THC_EINVAL;
   RCHK(need_built(ctx));
-  MISC(k_dot(ctx->P * ctx->P, ctx->Th, ctx->Th, ctx->scal + 40, ctx->stream));
+  MISC(k_dot(ctx->P * ctx->P, ctx->Th, ctx->Th, ctx->scal + 40, ctx->gws, ctx->stream));
   MISC(k_guess_features(ctx->P, ctx->o, ctx->v, ctx->Th, ctx->e, ctx->eps, ctx->scal + 40, phi, ctx->stream));
   return THC_OK;
 }
