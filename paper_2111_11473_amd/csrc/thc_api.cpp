@@ -1269,6 +1269,7 @@ struct thc_mlp {
         *d2 = nullptr, *d1 = nullptr;
   short* wb = nullptr;
   float* bb = nullptr;
+  float* tpart = nullptr;  // partial sums of the three-launch training step (allocated by its first call)
   bool packed = false;
   float* scratch = nullptr;            // device address of the allocation-free pass's scratch
   hipError_t scratch_err = hipSuccess;  // why it could not be looked up, if it could not
@@ -1341,8 +1342,21 @@ int mlp_fwd(thc_mlp* ctx, const float* X, int64_t R) {
   return mlp_fwd_into(ctx, X, R, MlpActs{ctx->xn, ctx->z1, ctx->h1, ctx->z2, ctx->h2, ctx->yn});
 }
 
-// loss and gradient (into ctx->g) of the mean squared error on normalized targets
-int mlp_bwd(thc_mlp* ctx, const float* X, const float* T, int64_t R) {
+// loss and gradient (into ctx->g) of the mean squared error on normalized targets and, for lr > 0,
+// one Adam step.  Networks of the guess network's class (width 256, at most 16 inputs and outputs)
+// take the three-launch path at every row count (4096 rows: see mlp.hip); other shapes the general
+// products.
+int mlp_step(thc_mlp* ctx, const float* X, const float* T, int64_t R, float lr) {
+  constexpr float B1 = 0.9f, B2 = 0.999f, EPS = 1e-8f;
+  const int64_t step = ctx->step + 1;
+  if (mlp_infer_supported(ctx->n_in, ctx->w, ctx->n_out)) {
+    if (!ctx->tpart) RCHK(mlp_alloc(ctx, &ctx->tpart, (size_t)mlp_train_floats(ctx->n_in, ctx->n_out), ctx->allocs));
+    HIPCHK(mlp_train(R, ctx->n_in, ctx->n_out, X, T, ctx->mu_in, ctx->sd_in, ctx->mu_out, ctx->sd_out, ctx->p, ctx->h1,
+                     ctx->d2, ctx->tpart, ctx->part, ctx->loss, ctx->g, ctx->m, ctx->v, lr, B1, B2, EPS, step,
+                     ctx->stream));
+    if (lr > 0.0f) ctx->step = step;
+    return THC_OK;
+  }
   const int64_t ni = ctx->n_in, w = ctx->w, no = ctx->n_out;
   const float *W2 = ctx->p + ni * w + w, *W3 = W2 + w * w + w;
   float *gW1 = ctx->g, *gb1 = gW1 + ni * w, *gW2 = gb1 + w, *gb2 = gW2 + w * w, *gW3 = gb2 + w, *gb3 = gW3 + w * no;
@@ -1357,6 +1371,10 @@ int mlp_bwd(thc_mlp* ctx, const float* X, const float* T, int64_t R) {
   HIPCHK(mlp_sgemm(false, true, 3, R, w, w, ctx->d2, w, W2, w, ctx->d1, w, nullptr, ctx->z1, w, s));
   HIPCHK(mlp_sgemm(true, false, 0, ni, w, R, ctx->xn, ni, ctx->d1, w, gW1, w, nullptr, nullptr, 0, s));
   HIPCHK(mlp_colsum(R, w, ctx->d1, gb1, s));
+  if (lr > 0.0f) {
+    HIPCHK(mlp_adam(ctx->np, ctx->p, ctx->g, ctx->m, ctx->v, lr, B1, B2, EPS, step, s));
+    ctx->step = step;
+  }
   return THC_OK;
 }
 
@@ -2658,7 +2676,7 @@ int thc_mlp_forward_noalloc(thc_mlp* ctx, const float* X, int64_t rows, float* Y
 int thc_mlp_loss_grad(thc_mlp* ctx, const float* X, const float* T, int64_t rows, float* loss, float* grad) {
   if (!ctx || !X || !T || rows < 1) return THC_EINVAL;
   RCHK(mlp_reserve(ctx, rows));
-  RCHK(mlp_bwd(ctx, X, T, rows));
+  RCHK(mlp_step(ctx, X, T, rows, 0.0f));
   if (grad) HIPCHK(hipMemcpyAsync(grad, ctx->g, ctx->np * sizeof(float), hipMemcpyDeviceToDevice, ctx->stream));
   if (loss) {
     RCHK(d2h(ctx, loss, ctx->loss, sizeof(float)));
@@ -2669,9 +2687,7 @@ int thc_mlp_loss_grad(thc_mlp* ctx, const float* X, const float* T, int64_t rows
 int thc_mlp_train_step(thc_mlp* ctx, const float* X, const float* T, int64_t rows, float lr, float* loss) {
   if (!ctx || !X || !T || rows < 1 || !(lr > 0.0f)) return THC_EINVAL;
   RCHK(mlp_reserve(ctx, rows));
-  RCHK(mlp_bwd(ctx, X, T, rows));
-  ctx->step += 1;
-  HIPCHK(mlp_adam(ctx->np, ctx->p, ctx->g, ctx->m, ctx->v, lr, 0.9f, 0.999f, 1e-8f, ctx->step, ctx->stream));
+  RCHK(mlp_step(ctx, X, T, rows, lr));
   ctx->packed = false;
   if (loss) {
     RCHK(d2h(ctx, loss, ctx->loss, sizeof(float)));
