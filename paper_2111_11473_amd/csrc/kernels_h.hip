@@ -433,77 +433,30 @@ hipError_t launch(int64_t Pp, int64_t Xb, int64_t ldi, int64_t nI, const TE* E, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// FP32 instantiation for the mixed-precision path: E, F and G in FP32, FP32 arithmetic and FP32
-// accumulation over one grid-point chunk, added into the FP64 H at its end.  With 4-byte
-// accumulators a wave holds an 8 (Y) x 8 (Z) patch (64 + 64 mirror accumulators in 128 VGPRs),
-// so a workgroup of four waves owns a whole 16 x 16 (Y, Z) block pair: per output a third of the
-// LDS reads and half the copied bytes of the FP64 kernel.  G is stored in 16 x 16 blocks
-// ([I][Pp/16][Pp/16][16][16]); the tile's G^YZ block (Yb, Zb) is copied as it is, its G^ZY block
-// (Zb, Yb) with its 16-byte granules swizzled (row zz, granule g at position 4 zz + (g ^ ((zz / 2)
-// % 4))), so that the column pieces a wave broadcasts from it fall on distinct LDS banks.  G is
-// broadcast into the FMAs by DPP row_newbcast as in the FP64 kernel (16 values to a VGPR).
-constexpr int W8 = 8;                           // patch edge (Y and Z) per wave
+// FP32 kernel of the mixed-precision path: E, F and G in FP32, FP32 arithmetic and FP32 accumulation
+// over one grid-point chunk, added into the FP64 H at its end.
+//
+// FP32 vector instructions issue at twice the FP64 rate from two waves of a SIMD, but not with a DPP
+// source: the product mix (mul, fmac, two fmac) reaches 139 TFLOP/s with plain VGPR operands and 80
+// with G broadcast by DPP.  So no factor is broadcast here.  The 64 lanes are 16 (X) x 4 (Z); a lane
+// holds a 4 (X) x 4 (Y) x 4 (Z) patch -- the cube, which reads the fewest operands per product: 32
+// values each of E, F at (X, Y), of E, F at (X, Z) and of G^YZ, G^ZY, as 24 16-byte LDS reads for
+// 64 brackets -- and its 64 + 64 mirror accumulators.  A wave owns 64 X, 4 Y and 16 Z; the four waves
+// of a workgroup a whole 16 x 16 (Y, Z) block pair of one X tile.  A lane's X are the granules
+// (16 bytes: two X of a row pair) lx and lx + 16 of a row pair, so sixteen lanes read 256
+// consecutive bytes.  G is stored in 16 x 16 blocks ([I][Pp/16][Pp/16][16][16]).
 constexpr int S32_PAIR = 64 * 2 * 4;            // one row pair of 64 X (FP32): 512 bytes
 constexpr int S32_EY = 0, S32_FY = 8 * S32_PAIR, S32_EZ = 16 * S32_PAIR, S32_FZ = 24 * S32_PAIR;
 constexpr int S32_G = 32 * S32_PAIR, S32_GT = S32_G + 1024, S32_STAGE = S32_GT + 1024;  // 18 KB
 constexpr int S32_NS = 4;
 static_assert(S32_NS * S32_STAGE * 2 <= 160 * 1024, "two workgroups per CU");
 
-// One row j of the wave patch (eight Z): t_k = ey fz_k + ez_k fy, then acc_k += G^YZ t_k and
-// accm_k += G^ZY t_k, G broadcast from lane B + k of each row of 16 lanes (B = 8 (j % 2)).  Every
-// DPP read comes at least two instructions after the VALU write of its t_k.
-template <int B>
-__device__ inline void h_row32(float (&acc)[W8], float (&accm)[W8], float ey, float fy, const float (&ez)[W8],
-                               const float (&fz)[W8], float g, float gm) {
-  float t0, t1, t2, t3, t4, t5, t6, t7;
-  asm("v_mul_f32 %[t0], %[ey], %[f0]\n\t"
-      "v_mul_f32 %[t1], %[ey], %[f1]\n\t"
-      "v_mul_f32 %[t2], %[ey], %[f2]\n\t"
-      "v_mul_f32 %[t3], %[ey], %[f3]\n\t"
-      "v_mul_f32 %[t4], %[ey], %[f4]\n\t"
-      "v_mul_f32 %[t5], %[ey], %[f5]\n\t"
-      "v_mul_f32 %[t6], %[ey], %[f6]\n\t"
-      "v_mul_f32 %[t7], %[ey], %[f7]\n\t"
-      "v_fmac_f32 %[t0], %[e0], %[fy]\n\t"
-      "v_fmac_f32 %[t1], %[e1], %[fy]\n\t"
-      "v_fmac_f32 %[t2], %[e2], %[fy]\n\t"
-      "v_fmac_f32 %[t3], %[e3], %[fy]\n\t"
-      "v_fmac_f32 %[t4], %[e4], %[fy]\n\t"
-      "v_fmac_f32 %[t5], %[e5], %[fy]\n\t"
-      "v_fmac_f32 %[t6], %[e6], %[fy]\n\t"
-      "v_fmac_f32 %[t7], %[e7], %[fy]\n\t"
-      "v_fmac_f32_dpp %[a0], %[g], %[t0] row_newbcast:%[b0]\n\t"
-      "v_fmac_f32_dpp %[m0], %[gm], %[t0] row_newbcast:%[b0]\n\t"
-      "v_fmac_f32_dpp %[a1], %[g], %[t1] row_newbcast:%[b1]\n\t"
-      "v_fmac_f32_dpp %[m1], %[gm], %[t1] row_newbcast:%[b1]\n\t"
-      "v_fmac_f32_dpp %[a2], %[g], %[t2] row_newbcast:%[b2]\n\t"
-      "v_fmac_f32_dpp %[m2], %[gm], %[t2] row_newbcast:%[b2]\n\t"
-      "v_fmac_f32_dpp %[a3], %[g], %[t3] row_newbcast:%[b3]\n\t"
-      "v_fmac_f32_dpp %[m3], %[gm], %[t3] row_newbcast:%[b3]\n\t"
-      "v_fmac_f32_dpp %[a4], %[g], %[t4] row_newbcast:%[b4]\n\t"
-      "v_fmac_f32_dpp %[m4], %[gm], %[t4] row_newbcast:%[b4]\n\t"
-      "v_fmac_f32_dpp %[a5], %[g], %[t5] row_newbcast:%[b5]\n\t"
-      "v_fmac_f32_dpp %[m5], %[gm], %[t5] row_newbcast:%[b5]\n\t"
-      "v_fmac_f32_dpp %[a6], %[g], %[t6] row_newbcast:%[b6]\n\t"
-      "v_fmac_f32_dpp %[m6], %[gm], %[t6] row_newbcast:%[b6]\n\t"
-      "v_fmac_f32_dpp %[a7], %[g], %[t7] row_newbcast:%[b7]\n\t"
-      "v_fmac_f32_dpp %[m7], %[gm], %[t7] row_newbcast:%[b7]"
-      : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3]), [a4] "+v"(acc[4]),
-        [a5] "+v"(acc[5]), [a6] "+v"(acc[6]), [a7] "+v"(acc[7]), [m0] "+v"(accm[0]), [m1] "+v"(accm[1]),
-        [m2] "+v"(accm[2]), [m3] "+v"(accm[3]), [m4] "+v"(accm[4]), [m5] "+v"(accm[5]), [m6] "+v"(accm[6]),
-        [m7] "+v"(accm[7]), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [t4] "=&v"(t4),
-        [t5] "=&v"(t5), [t6] "=&v"(t6), [t7] "=&v"(t7)
-      : [ey] "v"(ey), [fy] "v"(fy), [e0] "v"(ez[0]), [e1] "v"(ez[1]), [e2] "v"(ez[2]), [e3] "v"(ez[3]),
-        [e4] "v"(ez[4]), [e5] "v"(ez[5]), [e6] "v"(ez[6]), [e7] "v"(ez[7]), [f0] "v"(fz[0]), [f1] "v"(fz[1]),
-        [f2] "v"(fz[2]), [f3] "v"(fz[3]), [f4] "v"(fz[4]), [f5] "v"(fz[5]), [f6] "v"(fz[6]), [f7] "v"(fz[7]),
-        [g] "v"(g), [gm] "v"(gm), [b0] "n"(B), [b1] "n"(B + 1), [b2] "n"(B + 2), [b3] "n"(B + 3),
-        [b4] "n"(B + 4), [b5] "n"(B + 5), [b6] "n"(B + 6), [b7] "n"(B + 7));
-}
+typedef float f4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void h32_kernel(int Pp, int Xb, int64_t ldi, int64_t nI, const float* __restrict__ E,
-                                                  const float* __restrict__ F, const float* __restrict__ G,
-                                                  double* __restrict__ H, const uint32_t* __restrict__ tiles,
-                                                  int flags) {
+__global__ __launch_bounds__(256, 2) void h32_kernel(int Pp, int Xb, int64_t ldi, int64_t nI,
+                                                     const float* __restrict__ E, const float* __restrict__ F,
+                                                     const float* __restrict__ G, double* __restrict__ H,
+                                                     const uint32_t* __restrict__ tiles, int flags) {
   __shared__ __attribute__((aligned(16))) char lds[S32_NS * S32_STAGE];
   const uint32_t tile = tiles[blockIdx.x];
   if (tile & EMPTY) return;  // whole workgroup, before any barrier
@@ -515,7 +468,7 @@ __global__ __launch_bounds__(256) void h32_kernel(int Pp, int Xb, int64_t ldi, i
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   __builtin_assume(w >= 0 && w < 4);
-  const int ly0 = (w & 1) * W8, lz0 = (w >> 1) * W8;
+  const int lx = lane & 15, lz = lane >> 4;
 
   // a diagonal block has no mirror: its G^ZY slots stay zero (never copied)
   if (!mirror)
@@ -523,21 +476,23 @@ __global__ __launch_bounds__(256) void h32_kernel(int Pp, int Xb, int64_t ldi, i
 #pragma unroll
       for (int b = 0; b < S32_NS; ++b) ((float*)(lds + b * S32_STAGE + S32_GT))[i] = 0.0f;
 
-  float acc[W8][W8], accm[W8][W8];
+  // acc[y][z][x]: H at Y = y0 + 4 w + y, Z = z0 + 4 lz + z, X = X0 + 32 (x / 2) + 2 lx + x % 2
+  float acc[4][4][4], accm[4][4][4];
 #pragma unroll
-  for (int j = 0; j < W8; ++j)
+  for (int y = 0; y < 4; ++y)
 #pragma unroll
-    for (int k = 0; k < W8; ++k) acc[j][k] = accm[j][k] = 0.0f;
+    for (int z = 0; z < 4; ++z)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[y][z][x] = accm[y][z][x] = 0.0f;
 
   // copies of one stage: wave w takes row chunks w, w + 4, w + 8, w + 12 (1 KB = two row pairs
-  // each: E^Y, F^Y, E^Z, F^Z four chunks apiece); wave 0 also the G^YZ block, wave 1 (off the
-  // diagonal) the G^ZY block, lane l fetching the source granule the swizzle puts at position l
+  // each: E^Y, F^Y, E^Z, F^Z four chunks apiece); wave 0 also the G^YZ block (Yb, Zb), wave 1 (off the
+  // diagonal) the G^ZY block (Zb, Yb)
   const unsigned voff_r = (unsigned)(lane >> 5) * S32_PAIR + (unsigned)(lane & 31) * 16u;
   const bool g_yz = w == 0, g_zy = w == 1 && mirror;
   const bool extra = g_yz || g_zy;
   const unsigned nb16 = (unsigned)Pp / 16u;
-  const int gz_row = lane >> 2, gz_gran = (lane & 3) ^ ((gz_row >> 1) & 3);
-  const unsigned voff_g = g_zy ? (unsigned)(gz_row * 16 + 4 * gz_gran) * 4u : (unsigned)lane * 16u;
+  const unsigned voff_g = (unsigned)lane * 16u;
   const unsigned so_g = (g_zy ? (unsigned)Zb * nb16 + (unsigned)Yb : (unsigned)Yb * nb16 + (unsigned)Zb) * 1024u;
   const int64_t PX = (int64_t)Pp * LANES;
   const int64_t PP = (int64_t)Pp * Pp;
@@ -563,19 +518,6 @@ __global__ __launch_bounds__(256) void h32_kernel(int Pp, int Xb, int64_t ldi, i
     g_at += dPP;
   };
 
-  // broadcast sources: lane l holds G^YZ[ly0 + 2 r + m / 8][lz0 + m % 8] and G^ZY[lz0 + m % 8][ly0 +
-  // 2 r + m / 8] (r = 0..3, m = l % 16); the G^ZY row zz = lz0 + m % 8 lies at granule position
-  // 4 zz + (g ^ ((zz / 2) % 4)) for its column granule g
-  const int m = lane & 15;
-  const int goff = (ly0 + (m >> 3)) * 16 + lz0 + (m & 7);
-  const int gzz = lz0 + (m & 7);
-  int gmoff[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int yy = ly0 + 2 * r + (m >> 3);
-    gmoff[r] = (gzz * 4 + ((yy >> 2) ^ ((gzz >> 1) & 3))) * 4 + (yy & 3);
-  }
-
   constexpr int D = S32_NS - 1;
   auto next = [](int b) { return b + 1 == S32_NS ? 0 : b + 1; };
   int sbuf = 0;
@@ -587,33 +529,44 @@ __global__ __launch_bounds__(256) void h32_kernel(int Pp, int Xb, int64_t ldi, i
   wait_pipe<4>((int)(issued > 0 ? issued - 1 : 0), extra);
   int buf = 0;
   auto consume = [&]() {
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(1);
     const char* __restrict__ st = lds + buf * S32_STAGE;
-    const float* __restrict__ sg = (const float*)(st + S32_G);
-    const float* __restrict__ sgt = (const float*)(st + S32_GT);
-    auto pair = [&](int off, int p) { return *(const f2*)(st + off + p * S32_PAIR + lane * 8); };
-    float ez[W8], fz[W8];
+    // rows 2 p, 2 p + 1 of a region at this lane's four X: v[row][x]
+    auto rows = [&](int off, int p, float (&r0)[4], float (&r1)[4]) {
+      const char* at = st + off + p * S32_PAIR + lx * 16;
 #pragma unroll
-    for (int q = 0; q < W8 / 2; ++q) {
-      const f2 a = pair(S32_EZ, lz0 / 2 + q), b = pair(S32_FZ, lz0 / 2 + q);
-      ez[2 * q] = a.x; ez[2 * q + 1] = a.y;
-      fz[2 * q] = b.x; fz[2 * q + 1] = b.y;
-    }
-    float g[4], gm[4];
+      for (int h = 0; h < 2; ++h) {
+        const f4 v = *(const f4*)(at + 256 * h);
+        r0[2 * h] = v[0]; r1[2 * h] = v[1]; r0[2 * h + 1] = v[2]; r1[2 * h + 1] = v[3];
+      }
+    };
+    float ez[4][4], fz[4][4];
+    f4 gm[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      g[r] = sg[goff + 32 * r];
-      gm[r] = sgt[gmoff[r]];
+    for (int p = 0; p < 2; ++p) {
+      rows(S32_EZ, 2 * lz + p, ez[2 * p], ez[2 * p + 1]);
+      rows(S32_FZ, 2 * lz + p, fz[2 * p], fz[2 * p + 1]);
     }
 #pragma unroll
-    for (int p = 0; p < W8 / 2; ++p) {
-      const f2 ey = pair(S32_EY, ly0 / 2 + p), fy = pair(S32_FY, ly0 / 2 + p);
-      h_row32<0>(acc[2 * p], accm[2 * p], ey.x, fy.x, ez, fz, g[p], gm[p]);
-      h_row32<8>(acc[2 * p + 1], accm[2 * p + 1], ey.y, fy.y, ez, fz, g[p], gm[p]);
+    for (int z = 0; z < 4; ++z) gm[z] = *(const f4*)(st + S32_GT + (4 * lz + z) * 64 + w * 16);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      float ey[2][4], fy[2][4];
+      rows(S32_EY, 2 * w + p, ey[0], ey[1]);
+      rows(S32_FY, 2 * w + p, fy[0], fy[1]);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int y = 2 * p + r;
+        const f4 g = *(const f4*)(st + S32_G + (4 * w + y) * 64 + lz * 16);
+#pragma unroll
+        for (int z = 0; z < 4; ++z)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            const float t = __builtin_fmaf(ez[z][x], fy[r][x], ey[r][x] * fz[z][x]);
+            acc[y][z][x] = __builtin_fmaf(g[z], t, acc[y][z][x]);
+            accm[y][z][x] = __builtin_fmaf(gm[z][y], t, accm[y][z][x]);
+          }
+      }
     }
-    __builtin_amdgcn_s_setprio(0);
-    __builtin_amdgcn_sched_barrier(0);
   };
   const int64_t steady = nI - D;
   for (int64_t I = 0; I < steady; ++I) {
@@ -630,30 +583,23 @@ __global__ __launch_bounds__(256) void h32_kernel(int Pp, int Xb, int64_t ldi, i
     buf = next(buf);
   }
 
-  // H (FP64, [Pp][Pp][Xb]) = or += the chunk's sums
-  const unsigned xrow = (unsigned)Xb * 8u;
-  const unsigned lo = (unsigned)lane * 8u;
-  const double* Hw = H + ((int64_t)(y0 + ly0) * Pp + z0 + lz0) * Xb + X0;
-  const double* Hm = H + ((int64_t)(z0 + lz0) * Pp + y0 + ly0) * Xb + X0;
-  const int64_t h_bytes = ((int64_t)(W8 - 1) * Pp + W8) * Xb * 8;
-  const __amdgpu_buffer_rsrc_t rh = rsrc(Hw, h_bytes);
-  const __amdgpu_buffer_rsrc_t rm = rsrc(Hm, h_bytes);
+  // H (FP64, [Pp][Pp][Xb]) = or += the chunk's sums, two X at a time
 #pragma unroll
-  for (int j = 0; j < W8; ++j)
+  for (int m = 0; m < 2; ++m) {
+    if (m == 1 && !mirror) break;
 #pragma unroll
-    for (int k = 0; k < W8; ++k) {
-      const unsigned o = (unsigned)(j * Pp + k) * xrow;
-      const double v = fresh ? (double)acc[j][k] : bload(rh, lo, o) + (double)acc[j][k];
-      bstore(v, rh, lo, o);
-    }
-  if (mirror) {
+    for (int y = 0; y < 4; ++y)
 #pragma unroll
-    for (int j = 0; j < W8; ++j)
+      for (int z = 0; z < 4; ++z) {
+        const int64_t Y = y0 + 4 * w + y, Z = z0 + 4 * lz + z;
+        double* at = H + (m ? Z * Pp + Y : Y * Pp + Z) * Xb + X0 + 2 * lx;
 #pragma unroll
-      for (int k = 0; k < W8; ++k) {
-        const unsigned o = (unsigned)(k * Pp + j) * xrow;
-        const double v = fresh ? (double)accm[j][k] : bload(rm, lo, o) + (double)accm[j][k];
-        bstore(v, rm, lo, o);
+        for (int h = 0; h < 2; ++h) {
+          const d2 v = m ? d2{(double)accm[y][z][2 * h], (double)accm[y][z][2 * h + 1]}
+                         : d2{(double)acc[y][z][2 * h], (double)acc[y][z][2 * h + 1]};
+          d2* p = (d2*)(at + 32 * h);
+          *p = fresh ? v : *p + v;
+        }
       }
   }
 }
