@@ -1,4 +1,5 @@
-// FP64 batched GEMM on the CDNA4 matrix cores (v_mfma_f64_16x16x4f64).
+// Batched GEMM on the CDNA4 matrix cores: FP64 (v_mfma_f64_16x16x4f64), and FP32 and split-BF16 products
+// of FP64 operands for the mixed-precision path.
 //
 // Every dense rank-index contraction of the THC-CCSD residual (the Khatri-Rao panel
 // products, the C T C^T chains, the ERI-core contractions) is a call of this kernel with a
@@ -6,13 +7,9 @@
 // factor depends on the contracted index) and a fused epilogue (elementwise product with a
 // third matrix, alpha/beta accumulation).
 //
-// Tiling: a 256-thread workgroup (4 wave64s in a 2x2 grid) owns a BM x BN tile of C and
-// walks K in steps of 16 through LDS.  Each wave owns a (BM/2) x (BN/2) sub-tile held as
-// (BM/32) x (BN/32) MFMA accumulators of 16x16 doubles.  The next K-slab is prefetched into
-// registers while the current one is multiplied.  Ragged M, N, K are handled by
+// A workgroup owns a BM x BN tile of C and walks K through LDS, its waves (2 x 2, or 2 x 4) an equal
+// share of the tile each, held as 16 x 16 MFMA accumulators.  Ragged M, N, K are handled by
 // zero-filled LDS tiles and masked stores, so no operand needs padding.
-#include <type_traits>
-
 #include "internal.h"
 
 namespace thc {
@@ -80,14 +77,13 @@ __device__ inline TileId tile_id(const Gemm& g) {
   return id;
 }
 
-// Epilogue by blocks of 16 rows: every load (C for beta, the Hadamard factor) of a block is
-// issued before its stores, so the loads overlap instead of waiting one by one behind stores
-// to possibly the same addresses.  acc[i][j][r] is output element r of the lane in 16 x 16
-// block (i, j) of the wave's (WM x WN) patch at (wm0, wn0): row lk + 4 r for the FP64 MFMA
-// (ROW4 false), row 4 lk + r for the FP32-accumulating ones; column lr.
-template <int TI, int TJ, bool ROW4, typename ACC>
+// Epilogue of the FP32-accumulating kernels by blocks of 16 rows: every load (C for beta, the
+// Hadamard factor) of a block is issued before its stores, so the loads overlap instead of waiting
+// one by one behind stores to possibly the same addresses.  acc[i][j][r] is output element r of the
+// lane (row 4 lk + r, column lr) in 16 x 16 block (i, j) of the wave's (WM x WN) patch at (wm0, wn0).
+template <int TI, int TJ>
 __device__ inline void epilogue(const Gemm& g, const TileId& id, int64_t wm0, int64_t wn0, int lr, int lk,
-                                const ACC (&acc)[TI][TJ]) {
+                                const flt4 (&acc)[TI][TJ]) {
   double* __restrict__ C = g.C ? g.C + id.b * g.sC + (int64_t)id.split * g.sSplit : nullptr;
   float* __restrict__ Cf = g.Cf ? g.Cf + id.b * g.sC + (int64_t)id.split * g.sSplit : nullptr;
   const double* __restrict__ H = g.hmul ? g.hmul + id.b * g.sH : nullptr;
@@ -100,7 +96,7 @@ __device__ inline void epilogue(const Gemm& g, const TileId& id, int64_t wm0, in
     for (int j = 0; j < TJ; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t m = id.m0 + wm0 + i * 16 + (ROW4 ? 4 * lk + r : lk + 4 * r);
+        const int64_t m = id.m0 + wm0 + i * 16 + 4 * lk + r;
         const int64_t n = id.n0 + wn0 + j * 16 + lr;
         const bool ok = m < g.M && n < g.N;
         off[j][r] = ok ? c_offset(g, m, n) : -1;
@@ -119,8 +115,8 @@ __device__ inline void epilogue(const Gemm& g, const TileId& id, int64_t wm0, in
   }
 }
 
-// F32: operands rounded to FP32 on their way into LDS, v_mfma_f32_16x16x4f32 with FP32
-// accumulation (the mixed-precision path); otherwise FP64 throughout.
+// FP32 products of FP64 operands (the mixed-precision path): operands rounded to FP32 on their way
+// into LDS, v_mfma_f32_16x16x4f32 with FP32 accumulation, K in slabs of 16.
 //
 // Loads are branch-free: an element outside the matrix is read from the tile origin (always
 // inside) and replaced by zero when it is written to LDS, and the k-indexed scaling is applied
@@ -129,10 +125,8 @@ __device__ inline void epilogue(const Gemm& g, const TileId& id, int64_t wm0, in
 // to a per-tile base pointer.
 // SHORT (K of at most four slabs): the loads of every slab are issued at once, so a tile waits
 // for memory once rather than once per slab; the slabs then pass through the two LDS buffers.
-template <int BM, int BN, bool TA, bool TB, bool F32, int OCC, bool SHORT>
-__global__ __launch_bounds__(256, OCC) void dgemm_kernel(const Gemm g, const int64_t kchunk) {
-  using TL = typename std::conditional<F32, float, double>::type;
-  using ACC = typename std::conditional<F32, flt4, dbl4>::type;
+template <int BM, int BN, bool TA, bool TB, int OCC, bool SHORT>
+__global__ __launch_bounds__(256, OCC) void fgemm_kernel(const Gemm g, const int64_t kchunk) {
   constexpr int WM = BM / 2, WN = BN / 2;
   constexpr int TI = WM / 16, TJ = WN / 16;
   constexpr int NA = BM * BK / 256, NB = BN * BK / 256;
@@ -140,8 +134,8 @@ __global__ __launch_bounds__(256, OCC) void dgemm_kernel(const Gemm g, const int
   // k-rows a wave writes fall on distinct banks); one stored m- or n-fastest is copied row by
   // row (pitch of 32 banks mod 64: consecutive k-rows on opposite halves of the banks)
   constexpr int PA = BM + (TA ? 16 : 1), PB = BN + (TB ? 1 : 16);
-  __shared__ TL As[2][BK][PA];
-  __shared__ TL Bs[2][BK][PB];
+  __shared__ float As[2][BK][PA];
+  __shared__ float Bs[2][BK][PB];
 
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
@@ -195,16 +189,16 @@ __global__ __launch_bounds__(256, OCC) void dgemm_kernel(const Gemm g, const int
   };
   auto store = [&](int buf) {
 #pragma unroll
-    for (int r = 0; r < NA; ++r) As[buf][ka][ma + SMA * r] = (TL)(ra[r] * rsa);
+    for (int r = 0; r < NA; ++r) As[buf][ka][ma + SMA * r] = (float)(ra[r] * rsa);
 #pragma unroll
-    for (int r = 0; r < NB; ++r) Bs[buf][kb][nb + SNB * r] = (TL)(rb[r] * rsb);
+    for (int r = 0; r < NB; ++r) Bs[buf][kb][nb + SNB * r] = (float)(rb[r] * rsb);
   };
 
-  ACC acc[TI][TJ];
+  flt4 acc[TI][TJ];
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) acc[i][j] = ACC{0, 0, 0, 0};
+    for (int j = 0; j < TJ; ++j) acc[i][j] = flt4{0, 0, 0, 0};
 
   const int lr = lane & 15, lk = lane >> 4;
   // nk: how many k of the slab hold data (the rest are zeros); k-steps of 4 past them are skipped
@@ -215,7 +209,7 @@ __global__ __launch_bounds__(256, OCC) void dgemm_kernel(const Gemm g, const int
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 4) {
       if (kk >= nk) break;
-      TL af[TI], bf[TJ];
+      float af[TI], bf[TJ];
 #pragma unroll
       for (int i = 0; i < TI; ++i) af[i] = As[buf][kk + lk][wm * WM + i * 16 + lr];
 #pragma unroll
@@ -224,10 +218,7 @@ __global__ __launch_bounds__(256, OCC) void dgemm_kernel(const Gemm g, const int
       for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j)
-          if constexpr (F32)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i], bf[j], acc[i][j], 0, 0, 0);
-          else
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[i], bf[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i], bf[j], acc[i][j], 0, 0, 0);
     }
     if constexpr (!SHORT) __builtin_amdgcn_s_setprio(0);
   };
@@ -282,7 +273,290 @@ __global__ __launch_bounds__(256, OCC) void dgemm_kernel(const Gemm g, const int
     if (nslab > 0) compute(buf);
   }
 
-  epilogue<TI, TJ, F32>(g, id, wm * WM, wn * WN, lr, lk, acc);
+  epilogue<TI, TJ>(g, id, wm * WM, wn * WN, lr, lk, acc);
+}
+
+// FP64 products on operands copied straight into LDS (no VGPR on the way): the kernel of every FP64
+// product with K > 64.
+//
+// What bounds a large product here is the SIMD's register ports next to the matrix core: an FP64
+// MFMA takes 64 cycles, and everything that writes VGPRs beside it -- operand loads, LDS reads, the
+// scaling multiplies of a staged copy -- costs its issue and port cycles on top (the staged kernel
+// reached 62 TFLOP/s at 8192^3 where back-to-back MFMAs reach 72).  So a stage (8 k of a BM x BN
+// tile) goes to LDS by 16-byte buffer copies, NS stages deep, one barrier per stage, and is read as
+// 16-byte operands only: two k of a row (k-fastest operand) or two rows of one k (m- or n-fastest).
+//   k-fastest: LDS [row][4 granules of two k], granule g of row m at position g ^ (m / 4 % 4), so the
+//     sixteen rows of a read fall on distinct banks; lane (lr, lk) reads k = 2 lk, 2 lk + 1 of row lr;
+//   m-fastest: LDS [k][row], lane (lr, lk) reads rows 2 lr, 2 lr + 1 of k = 2 lk + s, one for each of
+//     two MFMA blocks (row i of block e is row 2 i + e of a 32-row group).
+// Both take step s's k of lane group lk as 2 lk + s.  A copy's granules past the matrix read zero
+// (the buffer ends at its last element); the columns k >= K that a k-fastest operand's last stage
+// picks up from the next rows are zeroed in LDS before use.  k-scale factors of a stage are copied to
+// LDS too, and the factor of both operands multiplies the A operand as it is read.
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
+
+// A buffer from base (uniform) of n doubles, n >= 0, at most 2^31 - 1 bytes.
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_n(const double* base, int64_t n) {
+  const uint64_t a = (uint64_t)base;
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  const int top = __builtin_amdgcn_readfirstlane((int)(n >> 28)), low = __builtin_amdgcn_readfirstlane((int)n);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(hi << 32 | lo), (short)0, top ? 0x7fffffff : low << 3, RSRC_W3);
+}
+// 16 (4) bytes per lane from a buffer straight into LDS at lds + 16 (4) lane
+__device__ inline void copy_lds16(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t voff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, 0u, 0, 0);
+}
+__device__ inline void copy_lds4(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t voff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 4, voff, 0u, 0, 0);
+}
+// At most n of this wave's copies outstanding and its LDS reads done, then the workgroup barrier.
+template <int N>
+__device__ inline void wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+template <int BM, int BN, int NWM, int NWN, bool TA, bool TB, bool SCALE, int NS, int OCC>
+__global__ __launch_bounds__(64 * NWM * NWN, OCC) void dgemm_lds_kernel(const Gemm g, const int64_t kchunk) {
+  constexpr int SK = 8;                                  // k per stage
+  constexpr int NW = NWM * NWN, WM = BM / NWM, WN = BN / NWN, TI = WM / 16, TJ = WN / 16;
+  constexpr int CA = BM * SK * 8 / 1024 / NW, CB = BN * SK * 8 / 1024 / NW;  // 1 KB copies per wave and stage
+  constexpr int AD = BM * SK, BD = BN * SK, STAGE = AD + BD + (SCALE ? 64 : 0);  // doubles
+  static_assert(TI % 2 == 0 && TJ % 2 == 0 && CA >= 1 && CB >= 1, "whole operand pairs and copies");
+  __shared__ __attribute__((aligned(16))) double lds[NS * STAGE];
+
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wave / NWN, wn = wave % NWN, lr = lane & 15, lk = lane >> 4;
+  const TileId id = tile_id<BM, BN>(g);
+  const int64_t b = id.b, m0 = id.m0, n0 = id.n0;
+  const int64_t kbeg = (int64_t)id.split * kchunk;
+  const int64_t kend = (kbeg + kchunk < g.K) ? kbeg + kchunk : g.K;
+  const double* __restrict__ A = g.A + b * g.sA + (TA ? m0 : m0 * g.lda);
+  const double* __restrict__ B = g.B + b * g.sB + (TB ? n0 * g.ldb : n0);
+  const int mlim = (int)((g.M - m0 < BM) ? g.M - m0 : BM), nlim = (int)((g.N - n0 < BN) ? g.N - n0 : BN);
+
+  // Byte offset of this lane's granule of copy c (of the operand's 1 KB copies) from the stage origin.
+  constexpr uint32_t OOB = 0x80000000u;
+  auto granule = [&](int c, int edge, bool kfast, uint32_t ld, int lim) -> uint32_t {
+    const int gid = c * 64 + lane;
+    if (kfast) {
+      const int row = gid >> 2, q = (gid & 3) ^ ((row >> 2) & 3);
+      return row < lim ? 8u * ((uint32_t)row * ld + 2u * (uint32_t)q) : OOB;
+    }
+    const int k = gid / (edge / 2), q = gid % (edge / 2);
+    return 2 * q < lim ? 8u * ((uint32_t)k * ld + 2u * (uint32_t)q) : OOB;
+  };
+  uint32_t va[CA], vb[CB];
+#pragma unroll
+  for (int c = 0; c < CA; ++c) va[c] = granule(wave * CA + c, BM, !TA, (uint32_t)g.lda, mlim);
+#pragma unroll
+  for (int c = 0; c < CB; ++c) vb[c] = granule(wave * CB + c, BN, TB, (uint32_t)g.ldb, nlim);
+  // scale factors: eight of each operand as sixteen 4-byte pieces, A's by wave 0, B's by wave 1
+  const double* sc = SCALE ? (wave == 0 ? g.kscaleA : wave == 1 ? g.kscaleB : nullptr) : nullptr;
+  const int64_t scs = wave == 0 ? g.ksA : g.ksB;
+  if (SCALE && sc) sc += b * (wave == 0 ? g.sksA : g.sksB);
+  const bool extra = SCALE && sc != nullptr;
+  const uint32_t vs = lane < 16 ? (uint32_t)(8 * (lane >> 1) * scs + 4 * (lane & 1)) : OOB;
+
+  // origins of the next stage to copy and the doubles from there to the operands' last elements
+  const int64_t stepA = SK * (TA ? g.lda : 1), stepB = SK * (TB ? 1 : g.ldb), stepS = SK * scs;
+  const double *pA = A + (TA ? kbeg * g.lda : kbeg), *pB = B + (TB ? kbeg : kbeg * g.ldb), *pS = sc;
+  int64_t remA = TA ? (g.K - 1 - kbeg) * g.lda + (g.M - m0) : (g.M - 1 - m0) * g.lda + (g.K - kbeg);
+  int64_t remB = TB ? (g.N - 1 - n0) * g.ldb + (g.K - kbeg) : (g.K - 1 - kbeg) * g.ldb + (g.N - n0);
+  int64_t remS = (g.K - 1 - kbeg) * scs + 1;
+  if (extra) pS += kbeg * scs;
+  auto stage_in = [&](int slot) {
+    double* at = lds + slot * STAGE;
+    const __amdgpu_buffer_rsrc_t rA = rsrc_n(pA, remA), rB = rsrc_n(pB, remB);
+#pragma unroll
+    for (int c = 0; c < CA; ++c) copy_lds16(rA, at + (wave * CA + c) * 128, va[c]);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) copy_lds16(rB, at + AD + (wave * CB + c) * 128, vb[c]);
+    if (extra) copy_lds4(rsrc_n(pS, remS), at + AD + BD + 32 * wave, vs);
+    pA += stepA;
+    pB += stepB;
+    remA -= stepA;
+    remB -= stepB;
+    if constexpr (SCALE) {
+      pS += stepS;
+      remS -= stepS;
+    }
+  };
+
+  dbl4 acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) acc[i][j] = dbl4{0, 0, 0, 0};
+
+  // Operands of one stage: o[s][i] for step s (k = 2 lk + s) and MFMA block i of the wave's rows.
+  auto operand = [&](const double* at, int edge, bool kfast, int base, auto& o) {
+    constexpr int T = sizeof(o[0]) / sizeof(double);
+    if (kfast) {
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const int row = base + 16 * i + lr;
+        const dbl2 x = *(const dbl2*)(at + row * SK + 2 * (lk ^ ((row >> 2) & 3)));
+        o[0][i] = x[0];
+        o[1][i] = x[1];
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < T; i += 2) {
+          const dbl2 x = *(const dbl2*)(at + (2 * lk + s) * edge + base + 16 * i + 2 * lr);
+          o[s][i] = x[0];
+          o[s][i + 1] = x[1];
+        }
+    }
+  };
+  // mid(): the next copies, issued between the two steps so that the products cover them (+4%)
+  auto compute = [&](int slot, auto&& mid) {
+    const double* at = lds + slot * STAGE;
+    double a[2][TI], bo[2][TJ];
+    operand(at, BM, !TA, wm * WM, a);
+    operand(at + AD, BN, TB, wn * WN, bo);
+    if constexpr (SCALE) {
+      dbl2 f = dbl2{1.0, 1.0};
+      if (g.kscaleA) f = *(const dbl2*)(at + AD + BD + 2 * lk);
+      if (g.kscaleB) {
+        const dbl2 h = *(const dbl2*)(at + AD + BD + 32 + 2 * lk);
+        f[0] *= h[0];
+        f[1] *= h[1];
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < TI; ++i) a[s][i] *= f[s];
+    }
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if (s == 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        mid();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][i], bo[s][j], acc[i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+  };
+
+  const int nst = kend > kbeg ? (int)((kend - kbeg + SK - 1) / SK) : 0;
+  const int tail = (int)(kend - kbeg) - SK * (nst - 1);  // k of the last stage
+  int put = 0;  // stages issued
+  for (; put < NS - 1 && put < nst; ++put) stage_in(put);
+  constexpr int Q = CA + CB;
+  auto ready = [&](int later) {  // wait for the oldest stage with `later` stages still in flight
+    if (later >= NS - 2) {
+      if (extra) wait_barrier<(NS - 2) * (Q + 1)>(); else wait_barrier<(NS - 2) * Q>();
+    } else if (NS > 3 && later == 1) {
+      if (extra) wait_barrier<Q + 1>(); else wait_barrier<Q>();
+    } else {
+      wait_barrier<0>();
+    }
+  };
+  int slot = 0, pslot = put % NS;
+  for (int st = 0; st < nst; ++st) {
+    ready(put - st - 1);  // and every wave is done with the stage whose slot is filled next
+    if ((!TA || TB) && st == nst - 1 && tail < SK) {  // zero the k >= K columns of k-fastest operands
+      auto clear = [&](double* at, int rows) {
+        for (int e = t; e < rows * SK; e += 64 * NW) {
+          const int row = e / SK, k = e % SK;
+          if (k >= tail) at[row * SK + 2 * ((k >> 1) ^ ((row >> 2) & 3)) + (k & 1)] = 0.0;
+        }
+      };
+      if (!TA) clear(lds + slot * STAGE, BM);
+      if (TB) clear(lds + slot * STAGE + AD, BN);
+      __syncthreads();
+    }
+    compute(slot, [&]() {
+      if (put < nst) {
+        stage_in(pslot);
+        ++put;
+        pslot = pslot + 1 == NS ? 0 : pslot + 1;
+      }
+    });
+    slot = slot + 1 == NS ? 0 : slot + 1;
+  }
+
+  // Epilogue: output element r of block (i, j) is MFMA row lk + 4 r, column lr; two columns (n-fastest
+  // B) or two rows of an interleaved pair (m-fastest A, pair_rows) are stored together.
+  double* __restrict__ C = g.C + b * g.sC + (int64_t)id.split * g.sSplit;
+  const double* __restrict__ H = g.hmul ? g.hmul + b * g.sH : nullptr;
+  const bool rd = g.beta != 0.0;
+  const bool pairs_m = TA && g.pair_rows, pairs_n = !TB && !g.pair_rows;
+  auto row = [&](int i, int r) -> int64_t {
+    const int q = lk + 4 * r;
+    return m0 + wm * WM + (TA ? 32 * (i / 2) + 2 * q + (i & 1) : 16 * i + q);
+  };
+  auto col = [&](int j) -> int64_t { return n0 + wn * WN + (!TB ? 32 * (j / 2) + 2 * lr + (j & 1) : 16 * j + lr); };
+  auto value = [&](double x, int64_t m, int64_t n) {
+    x *= g.alpha;
+    return H ? x * H[m * g.ldh + n] : x;
+  };
+#pragma unroll
+  for (int i = 0; i < TI; i += 2) {
+    if (pairs_n || pairs_m) {
+      // a 2 x 2 group of blocks: pairs along n for both rows, or along m for both columns
+      int64_t off[2][TJ / 2][4][2];
+      dbl2 x[2][TJ / 2][4];
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int jp = 0; jp < TJ / 2; ++jp)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            // element u of the pair: row i + e, column 2 jp + u (pairs_n), or row i + u, column 2 jp + e
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const int bi = pairs_n ? i + e : i + u, bj = pairs_n ? 2 * jp + u : 2 * jp + e;
+              const int64_t m = row(bi, r), n = col(bj);
+              const bool ok = m < g.M && n < g.N;
+              off[e][jp][r][u] = ok ? c_offset(g, m, n) : -1;
+              x[e][jp][r][u] = ok ? value(pairs_n ? acc[i + e][2 * jp + u][r] : acc[i + u][2 * jp + e][r], m, n) : 0.0;
+              if (rd && ok) x[e][jp][r][u] += g.beta * C[off[e][jp][r][u]];
+            }
+          }
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int jp = 0; jp < TJ / 2; ++jp)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (off[e][jp][r][1] >= 0) *(dbl2u*)(C + off[e][jp][r][0]) = x[e][jp][r];
+            else if (off[e][jp][r][0] >= 0) C[off[e][jp][r][0]] = x[e][jp][r][0];
+          }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        int64_t off[TJ][4];
+        double x[TJ][4];
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int64_t m = row(i + e, r), n = col(j);
+            const bool ok = m < g.M && n < g.N;
+            off[j][r] = ok ? c_offset(g, m, n) : -1;
+            x[j][r] = ok ? value(acc[i + e][j][r], m, n) : 0.0;
+            if (rd && ok) x[j][r] += g.beta * C[off[j][r]];
+          }
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (off[j][r] >= 0) C[off[j][r]] = x[j][r];
+      }
+    }
+  }
 }
 
 // Split-BF16 products (the compensated mode of the mixed-precision path): every operand is
@@ -453,7 +727,7 @@ __global__ __launch_bounds__(256, 2) void bgemm_kernel(const Gemm g, const int64
   }
   if (nslab > 0) compute(buf);
 
-  epilogue<TI, TJ, true>(g, id, wm * WM, wn * WN, lr, lk, acc);
+  epilogue<TI, TJ>(g, id, wm * WM, wn * WN, lr, lk, acc);
 }
 
 // C = alpha sum_s W_s (times the Hadamard factor) + beta C for a product computed as ksplit
@@ -482,7 +756,7 @@ bool slab_offsets_fit(const Gemm& g, int BM, int BN) {
   return la < (int64_t(1) << 31) && lb < (int64_t(1) << 31);
 }
 
-template <int BM, int BN, bool F32, bool SHORT = false>
+template <int BM, int BN, bool SHORT = false>
 hipError_t launch_tile(const Gemm& g, int64_t kchunk, hipStream_t s) {
   constexpr int OCC = 2;  // two workgroups per CU: one multiplies while the other loads
   static_assert(BM == BN, "square tiles (the upper mode walks a triangle of them)");
@@ -493,11 +767,36 @@ hipError_t launch_tile(const Gemm& g, int64_t kchunk, hipStream_t s) {
   // byte offsets within a slab stay below 2^31 (the buffer range): a slab spans BK rows of a
   // k-major operand, or BM (BN) rows of an m- (n-) major one
   if (!slab_offsets_fit(g, BM, BN)) return hipErrorInvalidValue;
-  if (!g.transA && !g.transB) hipLaunchKernelGGL((dgemm_kernel<BM, BN, false, false, F32, OCC, SHORT>), grid, dim3(256), 0, s, g, kchunk);
-  else if (g.transA && !g.transB) hipLaunchKernelGGL((dgemm_kernel<BM, BN, true, false, F32, OCC, SHORT>), grid, dim3(256), 0, s, g, kchunk);
-  else if (!g.transA && g.transB) hipLaunchKernelGGL((dgemm_kernel<BM, BN, false, true, F32, OCC, SHORT>), grid, dim3(256), 0, s, g, kchunk);
-  else hipLaunchKernelGGL((dgemm_kernel<BM, BN, true, true, F32, OCC, SHORT>), grid, dim3(256), 0, s, g, kchunk);
+  if (!g.transA && !g.transB) hipLaunchKernelGGL((fgemm_kernel<BM, BN, false, false, OCC, SHORT>), grid, dim3(256), 0, s, g, kchunk);
+  else if (g.transA && !g.transB) hipLaunchKernelGGL((fgemm_kernel<BM, BN, true, false, OCC, SHORT>), grid, dim3(256), 0, s, g, kchunk);
+  else if (!g.transA && g.transB) hipLaunchKernelGGL((fgemm_kernel<BM, BN, false, true, OCC, SHORT>), grid, dim3(256), 0, s, g, kchunk);
+  else hipLaunchKernelGGL((fgemm_kernel<BM, BN, true, true, OCC, SHORT>), grid, dim3(256), 0, s, g, kchunk);
   return hipGetLastError();
+}
+
+template <int BM, int BN, int NWM, int NWN, bool TA, bool TB, bool SCALE, int NS, int OCC>
+hipError_t launch_lds(const Gemm& g, int64_t kchunk, hipStream_t s) {
+  const int64_t ntn = (g.N + BN - 1) / BN;
+  if (g.upper && BM != BN) return hipErrorInvalidValue;  // the upper mode walks a triangle of square tiles
+  dim3 grid((unsigned)(g.upper ? ntn * (ntn + 1) / 2 : ntn), (unsigned)(g.upper ? 1 : (g.M + BM - 1) / BM),
+            (unsigned)(g.batch * g.ksplit));
+  if ((uint64_t)grid.x * grid.y * grid.z >= (uint64_t(1) << 32)) return hipErrorInvalidValue;
+  if (!slab_offsets_fit(g, BM, BN)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((dgemm_lds_kernel<BM, BN, NWM, NWN, TA, TB, SCALE, NS, OCC>), grid, dim3(64 * NWM * NWN), 0, s, g,
+                     kchunk);
+  return hipGetLastError();
+}
+template <int BM, int BN, int NS, int OCC>
+hipError_t launch_lds_any(const Gemm& g, int64_t kchunk, hipStream_t s) {
+  const bool scale = g.kscaleA || g.kscaleB;
+#define LDS_GEMM(TA, TB)                                                              \
+  return scale ? launch_lds<BM, BN, 2, 2, TA, TB, true, NS, OCC>(g, kchunk, s)        \
+               : launch_lds<BM, BN, 2, 2, TA, TB, false, NS, OCC>(g, kchunk, s)
+  if (!g.transA && !g.transB) LDS_GEMM(false, false);
+  if (g.transA && !g.transB) LDS_GEMM(true, false);
+  if (!g.transA && g.transB) LDS_GEMM(false, true);
+  LDS_GEMM(true, true);
+#undef LDS_GEMM
 }
 
 template <int BM, int BN>
@@ -514,11 +813,24 @@ hipError_t launch_btile(const Gemm& g, int64_t kchunk, hipStream_t s) {
   return hipGetLastError();
 }
 
-// 128 x 128 tiles need enough of them and a K slice long enough to amortize their prologue and
-// epilogue; short-K products run on 64 x 64 tiles, up to eight workgroups per CU.
+// 128 x 128 tiles (FP32 and split products, and the symmetric FP64 ones) need enough of them and a K
+// slice long enough to amortize their prologue and epilogue; short-K products run on 64 x 64 tiles.
 bool big_tiles(const Gemm& g, int64_t kchunk) {
   const int64_t t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128) * g.batch * g.ksplit;
   return g.M >= 96 && g.N >= 96 && t128 >= 480 && kchunk > 64;
+}
+
+// FP64 products: 128 x 64 tiles (three workgroups a CU) or 64 x 64 ones (four).  A CU's matrix cores
+// work through its tiles one after the other, so a product takes about the most tiles any of the 256
+// CUs gets, times the tile's work; the small tile costs 11% more per flop (59 against 66 TFLOP/s at
+// 8192^3) but wastes less at the edges and in the last round, and spreads few tiles better (fewer
+// than two 128 x 64 tiles a CU: 64 x 64 measured faster, e.g. 34 against 37 us at 1984 x 620 x 279).
+bool tall_tiles(const Gemm& g) {
+  const int64_t per = g.batch * g.ksplit, n64 = (g.N + 63) / 64;
+  const int64_t tall = (g.M + 127) / 128 * n64 * per, small = (g.M + 63) / 64 * n64 * per;
+  if (!slab_offsets_fit(g, 128, 64)) return false;
+  if ((g.M + 63) / 64 > 65535) return true;  // the grid's row limit
+  return tall >= 512 && 2.0 * (double)((tall + 255) / 256) <= 1.11 * (double)((small + 255) / 256);
 }
 
 }  // namespace
@@ -597,17 +909,22 @@ hipError_t gemm_f64(const Gemm& g0, hipStream_t s) {
   int64_t kchunk = (g.K + g.ksplit - 1) / g.ksplit;
   kchunk = ((kchunk + BK - 1) / BK) * BK;
   if (kchunk == 0) kchunk = BK;
+  if (!g.f32 && !g.bf16x3) {
+    if (g.upper) {  // square tiles; C C^T-like products with enough of them on eight waves and 128 x 128
+      if (!g.transA && g.transB && !g.kscaleA && !g.kscaleB && big_tiles(g, kchunk))
+        return launch_lds<128, 128, 2, 4, false, true, false, 4, 4>(g, kchunk, s);
+      return launch_lds_any<64, 64, 4, 4>(g, kchunk, s);
+    }
+    const bool tall = tall_tiles(g);
+    if ((g.M + (tall ? 127 : 63)) / (tall ? 128 : 64) > 65535) return hipErrorInvalidValue;
+    return tall ? launch_lds_any<128, 64, 3, 3>(g, kchunk, s) : launch_lds_any<64, 64, 4, 4>(g, kchunk, s);
+  }
   const bool big = big_tiles(g, kchunk);
   if (big && (g.M + 127) / 128 > 65535) return hipErrorInvalidValue;
   if (!big && (g.M + 63) / 64 > 65535) return hipErrorInvalidValue;
   if (g.bf16x3) return big ? launch_btile<128, 128>(g, kchunk, s) : launch_btile<64, 64>(g, kchunk, s);
-  const bool shortk = kchunk <= 4 * BK;
-  if (g.f32) {
-    if (big) return launch_tile<128, 128, true>(g, kchunk, s);
-    return shortk ? launch_tile<64, 64, true, true>(g, kchunk, s) : launch_tile<64, 64, true>(g, kchunk, s);
-  }
-  if (big) return launch_tile<128, 128, false>(g, kchunk, s);
-  return shortk ? launch_tile<64, 64, false, true>(g, kchunk, s) : launch_tile<64, 64, false>(g, kchunk, s);
+  if (big) return launch_tile<128, 128>(g, kchunk, s);
+  return kchunk <= 4 * BK ? launch_tile<64, 64, true>(g, kchunk, s) : launch_tile<64, 64>(g, kchunk, s);
 }
 
 }  // namespace thc
