@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libthc.so")
-SOURCES = ["gemm_f64.hip", "kernels_misc.hip", "kernels_h.hip", "kernels_exch.hip", "mlp.hip", "synth_gen.hip", "cpals.hip", "thc_api.cpp", "hostla.cpp"]
+SOURCES = ["gemm_f64.hip", "kernels_misc.hip", "kernels_h.hip", "kernels_exch.hip", "mlp.hip", "synth_gen.hip", "cpals.hip", "eigen.hip", "thc_api.cpp", "hostla.cpp"]
 ARCH = os.environ.get("THC_OFFLOAD_ARCH", "gfx950")
 
 
@@ -30,7 +30,7 @@ def _flags(src: str) -> list[str]:
     # every source is compiled for gfx950 only (the .cpp files hold host code and no kernels);
     # packed FP32 instructions are disabled for every device compilation
     f += [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-    if src == "hostla.cpp":  # host-only set-up linear algebra: AVX2/FMA vectors of the EPYC hosts
+    if src == "hostla.cpp":  # host-only linear algebra: AVX2/FMA vectors of the EPYC hosts
         f += ["-Xarch_host", "-mavx2", "-Xarch_host", "-mfma"]
     return f
 

@@ -1,17 +1,12 @@
-// Host FP64 dense linear algebra used once at set-up (never in the iteration):
-//  * Cholesky factorization of small diagonal blocks (the blocked GPU factorization
-//    hands its 64x64 diagonal blocks here) and the inverse of a lower-triangular block;
-//  * the symmetric eigenproblem of the (N_P x N_P) Fock operator in the orthonormalized
-//    amplitude basis: Householder reduction to tridiagonal form followed by the implicit
-//    QL iteration with Wilkinson-type shifts, with the orthogonal transformations
-//    accumulated (Golub & Van Loan, Matrix Computations, Sec. 8.3).  The QL step sequence (shift
-//    from the leading 2 x 2 block, rotations chased up the tridiagonal) is the published tql2
-//    procedure of Bowdler, Martin, Reinsch & Wilkinson (Numer. Math. 11, 293-306, 1968).
+// Host FP64 dense linear algebra for small matrices (the DIIS overlap matrix, CP-ALS fallbacks,
+// working bases of rank below 64; larger set-up problems run on the device, eigen.hip):
+//  * Cholesky factorization and the inverse of a lower-triangular matrix;
+//  * the symmetric eigenproblem: Householder reduction to tridiagonal form followed by the implicit
+//    QL iteration, with the orthogonal transformations accumulated (Golub & Van Loan, Matrix
+//    Computations, Sec. 8.3).
 // All matrices are row-major.
 #include <algorithm>
 #include <cmath>
-#include <cstring>
-#include <thread>
 #include <vector>
 
 #include "hostla.h"
@@ -49,25 +44,21 @@ void host_tri_inverse_lower(int64_t n, const double* L, double* X) {
 
 namespace {
 
-// Apply a function to rows [0, n) in parallel chunks.
-// (Serial below min_n items, where starting threads costs more than it saves.)
-template <class Fn>
-void parallel_rows(int64_t n, Fn fn, int64_t min_n = 256) {
-  unsigned nt = std::thread::hardware_concurrency();
-  if (nt == 0) nt = 1;
-  if (nt > 16) nt = 16;
-  if (n < min_n || nt == 1) {
-    fn(0, n);
-    return;
+// Applies each plane rotation to rows i, i + 1 of Zt (columns of the eigenvector matrix) as it comes.
+struct RowRotations {
+  int64_t n;
+  double* Zt;
+  int sweep(int64_t, int64_t) { return 0; }
+  void rotate(int64_t i, double c, double s) {
+    double* z0 = Zt + i * n;
+    double* z1 = z0 + n;
+    for (int64_t k = 0; k < n; ++k) {
+      const double a0 = z0[k], a1 = z1[k];
+      z1[k] = s * a0 + c * a1;
+      z0[k] = c * a0 - s * a1;
+    }
   }
-  std::vector<std::thread> th;
-  const int64_t chunk = (n + nt - 1) / nt;
-  for (unsigned t = 0; t < nt; ++t) {
-    const int64_t a = t * chunk, b = std::min<int64_t>(n, a + chunk);
-    if (a < b) th.emplace_back(fn, a, b);
-  }
-  for (auto& x : th) x.join();
-}
+};
 
 }  // namespace
 
@@ -100,26 +91,20 @@ int host_syev(int64_t n, double* A, double* w) {
     vn = std::sqrt(vn);
     for (int64_t i = k + 1; i < n; ++i) vk[i] /= vn;
     // p = 2 A v on the trailing block
-    parallel_rows(n - k - 1, [&](int64_t a, int64_t b) {
-      for (int64_t r = a; r < b; ++r) {
-        const int64_t i = k + 1 + r;
-        const double* Ai = A + i * n;
-        double s = 0.0;
-        for (int64_t j = k + 1; j < n; ++j) s += Ai[j] * vk[j];
-        p[i] = 2.0 * s;
-      }
-    });
+    for (int64_t i = k + 1; i < n; ++i) {
+      const double* Ai = A + i * n;
+      double s = 0.0;
+      for (int64_t j = k + 1; j < n; ++j) s += Ai[j] * vk[j];
+      p[i] = 2.0 * s;
+    }
     double K = 0.0;
     for (int64_t i = k + 1; i < n; ++i) K += vk[i] * p[i];
     for (int64_t i = k + 1; i < n; ++i) q[i] = p[i] - K * vk[i];
-    parallel_rows(n - k - 1, [&](int64_t a, int64_t b) {
-      for (int64_t r = a; r < b; ++r) {
-        const int64_t i = k + 1 + r;
-        double* Ai = A + i * n;
-        const double vi = vk[i], qi = q[i];
-        for (int64_t j = k + 1; j < n; ++j) Ai[j] -= vi * q[j] + qi * vk[j];
-      }
-    });
+    for (int64_t i = k + 1; i < n; ++i) {
+      double* Ai = A + i * n;
+      const double vi = vk[i], qi = q[i];
+      for (int64_t j = k + 1; j < n; ++j) Ai[j] -= vi * q[j] + qi * vk[j];
+    }
     d[k] = A[k * n + k];
     e[k] = alpha;  // sub-diagonal element between k and k+1
   }
@@ -127,97 +112,24 @@ int host_syev(int64_t n, double* A, double* w) {
   e[n - 2] = A[(n - 1) * n + n - 2];
   d[n - 1] = A[(n - 1) * n + n - 1];
   e[n - 1] = 0.0;
-  // --- accumulate Q = H_0 ... H_{n-3}; stored transposed (row j of Zt = column j of Q) ---
-  // Zt = Q^T = H_{n-3} ... H_0 applied from the right to the identity: Zt <- Zt H_k for
-  // k = n-3 .. 0.  Rows of Zt are independent, so each thread takes blocks of 16 rows and applies
-  // every reflector to them while they stay in its cache (the reflectors stream past once per
-  // block instead of the whole matrix once per reflector).
+  // --- accumulate Q = H_0 ... H_{n-3}; stored transposed (row j of Zt = column j of Q): Zt <- Zt H_k
+  // for k = n-3 .. 0 from the identity ---
   std::vector<double> Zt((size_t)n * n, 0.0);
   for (int64_t i = 0; i < n; ++i) Zt[(size_t)i * n + i] = 1.0;
-  constexpr int64_t RB = 16;
-  parallel_rows((n + RB - 1) / RB, [&](int64_t a, int64_t b) {
-    for (int64_t blk = a; blk < b; ++blk) {
-      const int64_t r0 = blk * RB, r1 = std::min(n, r0 + RB);
-      for (int64_t k = n - 3; k >= 0; --k) {
-        const double* vk = &V[(size_t)k * n];
-        for (int64_t r = r0; r < r1; ++r) {
-          double* z = &Zt[(size_t)r * n];
-          double s = 0.0;
-          for (int64_t j = k + 1; j < n; ++j) s += z[j] * vk[j];
-          s *= 2.0;
-          if (s != 0.0)
-            for (int64_t j = k + 1; j < n; ++j) z[j] -= s * vk[j];
-        }
-      }
-    }
-  }, 2);
-  // --- implicit QL on the tridiagonal (d, e): e[i] couples i and i+1 ---
-  // The iteration itself needs only (d, e); its plane rotations (combining columns i, i+1 of Q,
-  // i.e. rows i, i+1 of Zt) are recorded in order and applied afterwards, each thread taking
-  // slices of 64 columns of Zt through the whole sequence (columns are independent, and a slice
-  // of every row stays in cache while the sweeps run over it).
-  struct Rot {
-    int64_t i;
-    double c, s;
-  };
-  std::vector<Rot> rots;
-  rots.reserve((size_t)n * 8);
-  for (int64_t l = 0; l < n; ++l) {
-    int iter = 0;
-    for (;;) {
-      int64_t m = l;
-      for (; m + 1 < n; ++m) {
-        const double dd = std::fabs(d[m]) + std::fabs(d[m + 1]);
-        if (std::fabs(e[m]) <= 1e-16 * dd) break;
-      }
-      if (m == l) break;
-      if (++iter > 80) return 2;
-      double g = (d[l + 1] - d[l]) / (2.0 * e[l]);
-      double r = std::hypot(g, 1.0);
-      g = d[m] - d[l] + e[l] / (g + (g >= 0 ? r : -r));
-      double s = 1.0, c = 1.0, pp = 0.0;
-      bool underflow = false;
-      for (int64_t i = m - 1; i >= l; --i) {
-        const double f = s * e[i];
-        const double b = c * e[i];
-        r = std::hypot(f, g);
-        e[i + 1] = r;
-        if (r == 0.0) {
-          d[i + 1] -= pp;
-          e[m] = 0.0;
-          underflow = true;
-          break;
-        }
-        s = f / r;
-        c = g / r;
-        g = d[i + 1] - pp;
-        r = (d[i] - g) * s + 2.0 * c * b;
-        pp = s * r;
-        d[i + 1] = g + pp;
-        g = c * r - b;
-        rots.push_back({i, c, s});
-      }
-      if (underflow) continue;
-      d[l] -= pp;
-      e[l] = g;
-      e[m] = 0.0;
+  for (int64_t k = n - 3; k >= 0; --k) {
+    const double* vk = &V[(size_t)k * n];
+    for (int64_t r = k + 1; r < n; ++r) {  // (rows up to k are still those of the identity)
+      double* z = &Zt[(size_t)r * n];
+      double s = 0.0;
+      for (int64_t j = k + 1; j < n; ++j) s += z[j] * vk[j];
+      s *= 2.0;
+      if (s != 0.0)
+        for (int64_t j = k + 1; j < n; ++j) z[j] -= s * vk[j];
     }
   }
-  constexpr int64_t CW = 64;
-  parallel_rows((n + CW - 1) / CW, [&](int64_t a, int64_t b) {
-    for (int64_t sl = a; sl < b; ++sl) {
-      const int64_t k0 = sl * CW, kw = std::min(n, k0 + CW) - k0;
-      for (const Rot& q : rots) {
-        double* z0 = &Zt[(size_t)q.i * n + k0];
-        double* z1 = z0 + n;
-        for (int64_t k = 0; k < kw; ++k) {
-          const double a0 = z0[k], a1 = z1[k];
-          z1[k] = q.s * a0 + q.c * a1;
-          z0[k] = q.c * a0 - q.s * a1;
-        }
-      }
-    }
-  }, 2);
+  // --- implicit QL on the tridiagonal (d, e): e[i] couples i and i+1 ---
+  RowRotations rows{n, Zt.data()};
+  if (const int rc = ql_iterate(n, d.data(), e.data(), rows)) return rc;
   // sort ascending, write eigenvectors into the columns of A
   std::vector<int64_t> idx(n);
   for (int64_t i = 0; i < n; ++i) idx[i] = i;

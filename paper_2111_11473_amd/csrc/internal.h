@@ -95,6 +95,25 @@ hipError_t k_mp2_denom(int64_t rows0, int64_t rows, int64_t ov, int64_t v, const
 hipError_t k_fill(int64_t n, double val, double* x, hipStream_t s);
 hipError_t k_set_diag(int64_t n, const double* d, double* X, int64_t ld, hipStream_t s);
 
+// Set-up linear algebra on the device (eigen.hip).
+// L (in place, zeros above the diagonal) and X = L^-1 (kb x kb) of a diagonal block, kb <= 64;
+// status[0] = blk + 1 at a pivot <= 0 unless it is set already.
+hipError_t eig_chol_block(int kb, double* A, int64_t lda, double* X, double* status, int64_t blk, hipStream_t s);
+// X = the inverse of the kb x kb lower-triangular matrix with M below the diagonal and dval on it (X may be M)
+hipError_t eig_tri_inverse(int kb, const double* M, double dval, double* X, hipStream_t s);
+hipError_t eig_symmetrize(int64_t n, const double* A, double* out, hipStream_t s);  // (A + A^T) / 2
+// Householder reduction of the symmetric A (n >= 2, overwritten) to the tridiagonal (d, e): unit (or
+// zero) reflector vectors in the rows 0 .. n - 3 of V.
+int64_t eig_tridiag_scratch(int64_t n);
+hipError_t eig_tridiag(int64_t n, double* A, double* V, double* d, double* e, double* scratch, hipStream_t s);
+// Plane rotations applied to the rows of Z (n x n).  table (16-byte aligned): as 64-bit integers the
+// number of groups (at most ROT_GROUPS) and for each its lowest row, its tiles of ROT_K + 1 steps and
+// the offset of its [step][ROT_K](c, s) table in doubles (a multiple of 2).
+constexpr int ROT_K = 16, ROT_GROUPS = 21, ROT_HEAD = 64;
+hipError_t eig_rotate(int64_t n, double* Z, const double* table, hipStream_t s);
+// out[i][j] = Z[idx[j]][i]
+hipError_t eig_gather_columns(int64_t n, const double* Z, const double* idx, double* out, hipStream_t s);
+
 // Synthetic inputs on the device (synth_gen.hip; values bit-identical to the Python generator).
 // out[i] = N(0,1) draw first + i of (seed, stream) / divisor.
 hipError_t synth_normals(uint64_t seed, uint64_t stream, uint64_t first, int64_t count, double divisor, double* out,

@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -57,6 +58,7 @@ struct thc_ctx {
   int64_t nb = 0, KS = 1, Xb = 0, Ic = 0, Xc = 0, X7 = 0;
 
   std::vector<void*> allocs;
+  size_t arena_bytes = 0;  // length of the library-allocated arena (0: the caller's workspace)
   size_t bytes = 0;
   void* ws = nullptr;            // caller's device workspace (thc_create_with_workspace), or null
   size_t ws_bytes = 0;
@@ -207,10 +209,6 @@ int h2d(Ctx* ctx, void* dev, const void* host, size_t bytes) {
   return THC_OK;
 }
 
-// rows x cols block of doubles with device row pitch ld (elements) <-> packed host rows
-int d2h_block(thc_ctx* ctx, double* host, const double* dev, int64_t ld, int64_t rows, int64_t cols);
-int h2d_block(thc_ctx* ctx, double* dev, int64_t ld, const double* host, int64_t rows, int64_t cols);
-
 hipEvent_t next_event(thc_ctx* ctx) {
   if (ctx->pool_used == ctx->pool.size()) {
     hipEvent_t ev;
@@ -309,49 +307,17 @@ int zero(thc_ctx* ctx, double* p, size_t count) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Dense SPD solves on the device: blocked right-looking Cholesky (lower, in place) whose
-// 64 x 64 diagonal blocks are factored and inverted on the host; the panel and trailing
-// updates are GEMMs.  Linv receives the inverses of the diagonal blocks.
+// Dense SPD solves on the device: blocked right-looking Cholesky (lower, in place); the panel and
+// trailing updates are GEMMs.  Linv receives the inverses of the 64 x 64 diagonal blocks.  The pivot
+// check stays on the device until the end (ctx->scal[61]: one more than the first failed block).
 constexpr int64_t CB = 64;
 
-int d2h_block(thc_ctx* ctx, double* host, const double* dev, int64_t ld, int64_t rows, int64_t cols) {
-  const size_t bytes = (size_t)(rows * cols) * sizeof(double);
-  void* p = pinned(ctx, bytes);
-  if (!p) { ctx->err = "pinned staging allocation failed"; return THC_ENOMEM; }
-  HIPCHK(hipMemcpy2DAsync(p, cols * sizeof(double), dev, ld * sizeof(double), cols * sizeof(double), rows,
-                          hipMemcpyDeviceToHost, ctx->stream));
-  HIPCHK(hipStreamSynchronize(ctx->stream));
-  std::memcpy(host, p, bytes);
-  return THC_OK;
-}
-
-int h2d_block(thc_ctx* ctx, double* dev, int64_t ld, const double* host, int64_t rows, int64_t cols) {
-  const size_t bytes = (size_t)(rows * cols) * sizeof(double);
-  void* p = pinned(ctx, bytes);
-  if (!p) { ctx->err = "pinned staging allocation failed"; return THC_ENOMEM; }
-  std::memcpy(p, host, bytes);
-  HIPCHK(hipMemcpy2DAsync(dev, ld * sizeof(double), p, cols * sizeof(double), cols * sizeof(double), rows,
-                          hipMemcpyHostToDevice, ctx->stream));
-  HIPCHK(hipStreamSynchronize(ctx->stream));
-  return THC_OK;
-}
-
 int potrf(thc_ctx* ctx, double* A, int64_t n, double* Linv, double* tmp, const char* what) {
-  std::vector<double> hb(CB * CB), hi(CB * CB);
+  RCHK(zero(ctx, ctx->scal + 61, 1));
   for (int64_t k0 = 0; k0 < n; k0 += CB) {
     const int64_t kb = std::min(CB, n - k0);
-    RCHK(d2h_block(ctx, hb.data(), A + k0 * n + k0, n, kb, kb));
-    if (host_cholesky(kb, hb.data()) != 0) {
-      char buf[160];
-      snprintf(buf, sizeof buf, "%s is not positive definite (Cholesky pivot <= 0 in diagonal block %lld of %lld)",
-               what, (long long)(k0 / CB), (long long)((n + CB - 1) / CB));
-      ctx->err = buf;
-      return THC_ESINGULAR;
-    }
-    host_tri_inverse_lower(kb, hb.data(), hi.data());
-    RCHK(h2d_block(ctx, A + k0 * n + k0, n, hb.data(), kb, kb));
     double* Li = Linv + (k0 / CB) * CB * CB;
-    RCHK(h2d(ctx, Li, hi.data(), kb * kb * sizeof(double)));
+    MISC(eig_chol_block((int)kb, A + k0 * n + k0, n, Li, ctx->scal + 61, k0 / CB, ctx->stream));
     const int64_t r0 = k0 + kb, rn = n - r0;
     if (rn <= 0) continue;
     // panel: A[r0:, k0:k0+kb] <- A[r0:, k0:k0+kb] L_kk^-T
@@ -359,6 +325,15 @@ int potrf(thc_ctx* ctx, double* A, int64_t n, double* Linv, double* tmp, const c
     MISC(k_copy2d(1, rn, kb, tmp, kb, 0, A + r0 * n + k0, n, 0, false, ctx->stream));
     // trailing: A[r0:, r0:] -= panel panel^T
     RCHK(gemm(ctx, mk(rn, rn, kb, A + r0 * n + k0, n, false, A + r0 * n + k0, n, true, A + r0 * n + r0, n, -1.0, 1.0)));
+  }
+  double status = 0.0;
+  RCHK(d2h(ctx, &status, ctx->scal + 61, sizeof(double)));
+  if (status != 0.0) {
+    char buf[160];
+    snprintf(buf, sizeof buf, "%s is not positive definite (Cholesky pivot <= 0 in diagonal block %lld of %lld)",
+             what, (long long)status - 1, (long long)((n + CB - 1) / CB));
+    ctx->err = buf;
+    return THC_ESINGULAR;
   }
   return THC_OK;
 }
@@ -383,6 +358,155 @@ int trsm(thc_ctx* ctx, const double* A, int64_t n, const double* Linv, double* B
     }
     MISC(k_copy2d(1, kb, m, tmp, m, 0, B + k0 * m, m, 0, false, ctx->stream));
   }
+  return THC_OK;
+}
+
+// ---------------------------------------------------------------------------------------
+// Symmetric eigenproblem on the device (eigen.hip).
+//
+// Collects the rotations of the QL iteration in tables (groups of ROT_K sweeps, see eig_rotate) in two
+// halves of pinned memory and starts each full half on its way: copy and rotations run on the
+// stream while the host fills the other half.
+class RotationStream {
+ public:
+  RotationStream(thc_ctx* c, int64_t n, double* Z, double* dev, int64_t dev_len) : ctx(c), n_(n), Z_(Z), dev_(dev) {
+    len_ = std::min<int64_t>(dev_len, std::max<int64_t>(1 << 16, ROT_HEAD + group_len(0))) & ~int64_t(1);
+  }
+  ~RotationStream() {
+    for (hipEvent_t e : ev_)
+      if (e) (void)hipEventDestroy(e);
+  }
+  // doubles of a group whose lowest row is l
+  int64_t group_len(int64_t l) const { return (n_ - 1 - l + ROT_K + ROT_K) / (ROT_K + 1) * (ROT_K + 1) * ROT_K * 2; }
+  int start() {
+    if (len_ < ROT_HEAD + group_len(0)) { ctx->err = "eigensolver: rotation table does not fit"; return THC_ENOMEM; }
+    host_ = (double*)pinned(ctx, 2 * len_ * sizeof(double));
+    if (!host_) { ctx->err = "pinned staging allocation failed"; return THC_ENOMEM; }
+    for (hipEvent_t& e : ev_) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    return THC_OK;
+  }
+  int sweep(int64_t l, int64_t m) {
+    close_sweep();
+    if (sweeps_ == 0 || sweeps_ == ROT_K) {
+      const int64_t glen = group_len(l);
+      if (groups_ == ROT_GROUPS || used_ + glen > len_) RCHK(flush());
+      int64_t* hdr = (int64_t*)half();
+      hdr[1 + 3 * groups_] = l;
+      hdr[2 + 3 * groups_] = glen / ((ROT_K + 1) * ROT_K * 2);
+      hdr[3 + 3 * groups_] = used_;
+      ++groups_;
+      begin_ = half() + used_;
+      used_ += glen;
+      end_ = half() + used_;
+      sweeps_ = 0;
+    }
+    at_ = begin_ + 2 * sweeps_;
+    identity(begin_ + 2 * (((n_ - 1 - m) + sweeps_) * ROT_K + sweeps_));  // pairs above the sweep
+    ++sweeps_;
+    return THC_OK;
+  }
+  void rotate(int64_t, double c, double s) {
+    at_[0] = c;
+    at_[1] = s;
+    at_ += 2 * ROT_K;
+  }
+  int finish() {
+    close_sweep();
+    if (sweeps_ > 0) {
+      for (; sweeps_ < ROT_K; ++sweeps_) {
+        at_ = begin_ + 2 * sweeps_;
+        identity(end_);
+      }
+      RCHK(flush());
+    }
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    return THC_OK;
+  }
+
+ private:
+  double* half() { return host_ + (which_ ? len_ : 0); }
+  void identity(const double* upto) {
+    for (; at_ < upto; at_ += 2 * ROT_K) {
+      at_[0] = 1.0;
+      at_[1] = 0.0;
+    }
+  }
+  void close_sweep() {
+    if (sweeps_ > 0) identity(end_);
+  }
+  int flush() {
+    if (groups_ == 0) return THC_OK;
+    ((int64_t*)half())[0] = groups_;
+    HIPCHK(hipMemcpyAsync(dev_, half(), used_ * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
+    HIPCHK(hipEventRecord(ev_[which_], ctx->stream));
+    busy_[which_] = true;
+    HIPCHK(eig_rotate(n_, Z_, dev_, ctx->stream));
+    which_ ^= 1;
+    if (busy_[which_]) HIPCHK(hipEventSynchronize(ev_[which_]));
+    groups_ = 0;
+    used_ = ROT_HEAD;
+    sweeps_ = 0;
+    return THC_OK;
+  }
+
+  thc_ctx* ctx;
+  int64_t n_, len_, used_ = ROT_HEAD;
+  double *Z_, *dev_, *host_ = nullptr, *begin_ = nullptr, *end_ = nullptr, *at_ = nullptr;
+  int sweeps_ = 0, groups_ = 0, which_ = 0;
+  bool busy_[2] = {false, false};
+  hipEvent_t ev_[2] = {nullptr, nullptr};
+};
+
+// Eigenvalues (ascending, host) and eigenvectors (columns of W) of the symmetric A (n x n, n >= EIG_DEV_MIN;
+// overwritten, like V and tab).  small: at least 64 n doubles; tab: at least 64 n.
+constexpr int64_t EIG_DEV_MIN = 64;  // below, the host's eigensolver: the tables need a longer scratch and
+                                     // a launch per column costs what the host takes for the whole problem
+
+int syev_device(thc_ctx* ctx, int64_t n, double* A, double* V, double* W, double* small, double* tab, int64_t tab_len,
+                std::vector<double>& w) {
+  hipStream_t s = ctx->stream;
+  double *dd = small, *de = small + n;
+  MISC(eig_tridiag(n, A, V, dd, de, small + 2 * n, s));
+  std::vector<double> de_h(2 * (size_t)n);
+  RCHK(d2h(ctx, de_h.data(), dd, 2 * n * sizeof(double)));
+  // Z = Q^T = (H_0 .. H_n-3)^T from the identity, the last block of reflectors first:
+  // Z <- Z (I - V T^T V^T) with T^-1 = I / 2 + the strict upper triangle of V^T V.  Rows and columns up
+  // to the block's first reflector are those of the identity.
+  double* Z = A;
+  RCHK(zero(ctx, Z, n * n));
+  MISC(k_fill(n, 1.0, small, s));
+  MISC(k_set_diag(n, small, Z, n, s));
+  for (int64_t k0 = (n - 3) / CB * CB; k0 >= 0; k0 -= CB) {
+    const int64_t kb = std::min(CB, n - 2 - k0), r0 = k0 + 1, m = n - r0;
+    const double* Vb = V + k0 * n + r0;  // kb x m
+    double* Zt = Z + r0 * n + r0;
+    RCHK(gemm(ctx, mk(kb, kb, m, Vb, n, false, Vb, n, true, tab, kb)));
+    MISC(eig_tri_inverse((int)kb, tab, 0.5, tab, s));  // T^T
+    RCHK(gemm(ctx, mk(m, kb, m, Zt, n, false, Vb, n, true, small, kb)));
+    RCHK(gemm(ctx, mk(m, kb, kb, small, kb, false, tab, kb, false, W, kb)));
+    RCHK(gemm(ctx, mk(m, m, kb, W, kb, false, Vb, n, false, Zt, n, -1.0, 1.0)));
+  }
+  double *d = de_h.data(), *e = d + n;
+  RotationStream rot(ctx, n, Z, tab, tab_len);
+  RCHK(rot.start());
+  const int rc = ql_iterate(n, d, e, rot);
+  if (rc == 2) ctx->err = "eigensolver did not converge";
+  if (rc != 0) {
+    (void)hipStreamSynchronize(s);
+    return rc == 2 ? THC_ENUMERIC : rc;
+  }
+  RCHK(rot.finish());
+  std::vector<double> idx(n);
+  std::vector<int64_t> ord(n);
+  for (int64_t i = 0; i < n; ++i) ord[i] = i;
+  std::sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) { return d[a] < d[b]; });
+  w.resize(n);
+  for (int64_t i = 0; i < n; ++i) {
+    idx[i] = (double)ord[i];
+    w[i] = d[ord[i]];
+  }
+  RCHK(h2d(ctx, small, idx.data(), n * sizeof(double)));
+  MISC(eig_gather_columns(n, Z, small, W, s));
   return THC_OK;
 }
 
@@ -646,14 +770,77 @@ int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
 
 // The plan for the context's budget (its workspace, else the device's free memory up to
 // MEM_CAP), then the arena and every buffer in it.
+// The arena of the context destroyed last, kept for the next one.  A freed block is cleared by the
+// driver before it can be allocated again, at about 38 GB/s, so that programs that set up one system
+// after another wait for it in hipMalloc once all memory has been handed out: 161 ms for the 6.2 GB of
+// o = 20, where the whole set-up takes 13 ms.  At most one block is held, of at most 1/32 of the
+// device's memory and only while half of that memory is free; a context that cannot use it (another
+// device, longer, or shorter than half of it) returns it to the driver before it allocates.  Blocks
+// come in with their work finished and belong to nobody while they are here, so any thread or
+// stream may take one.
+struct ArenaBlock {
+  void* p = nullptr;
+  size_t bytes = 0;
+  int device = 0;
+  ArenaBlock() = default;
+  ArenaBlock(const ArenaBlock&) = delete;
+  ArenaBlock& operator=(const ArenaBlock&) = delete;
+  ~ArenaBlock() { release(); }
+  void release() {
+    if (p) (void)hipFree(p);
+    p = nullptr;
+    bytes = 0;
+  }
+  void swap(ArenaBlock& o) {
+    std::swap(p, o.p);
+    std::swap(bytes, o.bytes);
+    std::swap(device, o.device);
+  }
+};
+std::mutex arena_mutex;
+ArenaBlock& arena_kept() {
+  static ArenaBlock* b = new ArenaBlock;  // (left to the end of the process)
+  return *b;
+}
+void arena_take(ArenaBlock& out) {
+  std::lock_guard<std::mutex> lock(arena_mutex);
+  out.swap(arena_kept());
+}
+void arena_keep(ArenaBlock& b) {  // b: afterwards what was kept before, or b itself if it is not kept
+  size_t freeb = 0, totalb = 0;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev != b.device || hipMemGetInfo(&freeb, &totalb) != hipSuccess) return;
+  if (b.bytes > totalb / 32 || freeb < totalb / 2) return;
+  std::lock_guard<std::mutex> lock(arena_mutex);
+  b.swap(arena_kept());
+}
+
+// hipMalloc that returns the kept arena to the driver before it gives up
+hipError_t device_alloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    ArenaBlock b;
+    arena_take(b);
+    if (b.p) {
+      b.release();
+      (void)hipGetLastError();
+      e = hipMalloc(p, bytes);
+    }
+  }
+  return e;
+}
+
 int plan_and_alloc(thc_ctx* ctx) {
   ctx->hslots = h_slots_per_xcd();
   if (ctx->hslots < 1) { ctx->err = "cannot query the device for the H-kernel launch"; return THC_EDEVICE; }
   double budget = (double)ctx->ws_bytes;
+  ArenaBlock kept;
   if (!ctx->ws) {
     size_t freeb = 0, totalb = 0;
+    arena_take(kept);
+    if (kept.p && kept.device != ctx->device) kept.release();
     if (hipMemGetInfo(&freeb, &totalb) != hipSuccess) { ctx->err = "hipMemGetInfo failed"; return THC_EDEVICE; }
-    budget = std::min(MEM_CAP, (double)freeb - 2.0e9);
+    budget = std::min(MEM_CAP, (double)freeb + (double)kept.bytes - 2.0e9);
   }
   RCHK(choose_plan(ctx, budget, ctx->hslots));
   const std::vector<uint32_t> tiles = h_tiles(ctx->Pp, ctx->Xb, ctx->hslots);
@@ -678,7 +865,16 @@ int plan_and_alloc(thc_ctx* ctx) {
     ctx->arena = (double*)ctx->ws;
   } else {
     void* q = nullptr;
-    if (hipMalloc(&q, total * sizeof(double)) != hipSuccess) {
+    if (kept.bytes >= total * sizeof(double) && kept.bytes / 2 <= total * sizeof(double)) {
+      q = kept.p;
+      ctx->arena_bytes = kept.bytes;
+      kept.p = nullptr;
+    } else {
+      kept.release();
+      ctx->arena_bytes = total * sizeof(double);
+      if (device_alloc(&q, ctx->arena_bytes) != hipSuccess) q = nullptr;
+    }
+    if (!q) {
       char buf[160];
       snprintf(buf, sizeof buf, "hipMalloc of the %.2f GB working memory failed", 8.0 * (double)total / 1e9);
       ctx->err = buf;
@@ -1282,7 +1478,7 @@ constexpr int64_t MLP_PARTS = 1024;
 template <class T>
 int mlp_alloc(thc_mlp* ctx, T** p, size_t count, std::vector<void*>& list) {
   void* q = nullptr;
-  if (hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T)) != hipSuccess) {
+  if (device_alloc(&q, std::max<size_t>(count, 1) * sizeof(T)) != hipSuccess) {
     (void)hipGetLastError();
     ctx->err = "hipMalloc failed";
     return THC_ENOMEM;
@@ -1664,17 +1860,18 @@ int thc_build_factors(thc_ctx* ctx, const double* L, const double* eps, const do
     rc = trsm(ctx, Sl, P, Linv, Em, P, false, tsolve); if (rc) break;
     MISC(k_copy2d(1, P, P, Em, P, 0, tmpw, P, 0, true, s));
     rc = trsm(ctx, Sl, P, Linv, tmpw, P, false, tsolve); if (rc) break;
-    std::vector<double> hC(PP), hw(P);
-    rc = d2h(ctx, hC.data(), tmpw, PP * sizeof(double)); if (rc) break;
-    for (int64_t i = 0; i < P; ++i)
-      for (int64_t j = 0; j < i; ++j) {
-        const double a = 0.5 * (hC[i * P + j] + hC[j * P + i]);
-        hC[i * P + j] = a;
-        hC[j * P + i] = a;
-      }
-    if (host_syev(P, hC.data(), hw.data()) != 0) { ctx->err = "eigensolver did not converge"; rc = THC_ENUMERIC; break; }
+    std::vector<double> hw(P);
+    MISC(eig_symmetrize(P, tmpw, Em, s));
+    if (P >= EIG_DEV_MIN) {
+      rc = syev_device(ctx, P, Em, tP, ctx->W, tsolve, tmpw, std::max(Q, P) * std::max<int64_t>(std::max(nL, P), CB), hw);
+      if (rc) break;
+    } else {
+      std::vector<double> hC(PP);
+      rc = d2h(ctx, hC.data(), Em, PP * sizeof(double)); if (rc) break;
+      if (host_syev(P, hC.data(), hw.data()) != 0) { ctx->err = "eigensolver did not converge"; rc = THC_ENUMERIC; break; }
+      rc = h2d(ctx, ctx->W, hC.data(), PP * sizeof(double)); if (rc) break;
+    }
     if (hw[0] <= 0.0) { ctx->err = "projected Fock operator is not positive"; rc = THC_ESINGULAR; break; }
-    rc = h2d(ctx, ctx->W, hC.data(), PP * sizeof(double)); if (rc) break;
     rc = h2d(ctx, ctx->e, hw.data(), P * sizeof(double)); if (rc) break;
     rc = trsm(ctx, Sl, P, Linv, ctx->W, P, true, tsolve); if (rc) break;   // W = L^-T V
 
@@ -2221,7 +2418,7 @@ struct CpWork {
   bool alloc() {
     size_t total = 0;
     for (const auto& w : want) total += w.second;
-    if (hipMalloc(&mem, total * sizeof(double)) != hipSuccess) {
+    if (device_alloc(&mem, total * sizeof(double)) != hipSuccess) {
       (void)hipGetLastError();
       mem = nullptr;
       return false;
@@ -2725,7 +2922,15 @@ const char* thc_last_error(const thc_ctx* ctx) { return ctx ? ctx->err.c_str() :
 
 void thc_destroy(thc_ctx* ctx) {
   if (!ctx) return;
-  (void)hipStreamSynchronize(ctx->stream);
+  const bool idle = hipStreamSynchronize(ctx->stream) == hipSuccess;
+  if (idle && ctx->arena_bytes > 0 && ctx->allocs.size() == 1) {
+    ArenaBlock b;
+    b.p = ctx->allocs[0];
+    b.bytes = ctx->arena_bytes;
+    b.device = ctx->device;
+    ctx->allocs.clear();
+    arena_keep(b);
+  }
   for (void* p : ctx->allocs) (void)hipFree(p);
   for (auto ev : ctx->pool) (void)hipEventDestroy(ev);
   if (ctx->pin) (void)hipHostFree(ctx->pin);
