@@ -28,9 +28,7 @@ __device__ inline int64_t c_offset(const Gemm& g, int64_t m, int64_t n) {
     const int sh = __builtin_ctz((unsigned)g.cblk);
     return ((((m >> 4) * (g.ldc >> sh) + (n >> sh)) << 4) + (m & 15)) * g.cblk + (n & (g.cblk - 1));
   }
-  if (g.pair_rows)
-    return g.xtile ? ((((n >> 6) * g.ldc + (m >> 1)) << 6) + (n & 63)) * 2 + (m & 1)
-                   : ((m >> 1) * g.ldc + n) * 2 + (m & 1);
+  if (g.xtile) return (((n >> 6) * g.ldc + m) << 6) + (n & 63);
   return m * g.ldc + n;
 }
 constexpr int RSRC_W3 = 0x00020000;  // raw 32-bit buffer access
@@ -488,11 +486,10 @@ __global__ __launch_bounds__(64 * NWM * NWN, OCC) void dgemm_lds_kernel(const Ge
   }
 
   // Epilogue: output element r of block (i, j) is MFMA row lk + 4 r, column lr; two columns (n-fastest
-  // B) or two rows of an interleaved pair (m-fastest A, pair_rows) are stored together.
+  // B) are stored together.
   double* __restrict__ C = g.C + b * g.sC + (int64_t)id.split * g.sSplit;
   const double* __restrict__ H = g.hmul ? g.hmul + b * g.sH : nullptr;
   const bool rd = g.beta != 0.0;
-  const bool pairs_m = TA && g.pair_rows, pairs_n = !TB && !g.pair_rows;
   auto row = [&](int i, int r) -> int64_t {
     const int q = lk + 4 * r;
     return m0 + wm * WM + (TA ? 32 * (i / 2) + 2 * q + (i & 1) : 16 * i + q);
@@ -504,8 +501,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, OCC) void dgemm_lds_kernel(const Ge
   };
 #pragma unroll
   for (int i = 0; i < TI; i += 2) {
-    if (pairs_n || pairs_m) {
-      // a 2 x 2 group of blocks: pairs along n for both rows, or along m for both columns
+    if constexpr (!TB) {
+      // a 2 x 2 group of blocks: pairs along n for both rows
       int64_t off[2][TJ / 2][4][2];
       dbl2 x[2][TJ / 2][4];
 #pragma unroll
@@ -514,14 +511,12 @@ __global__ __launch_bounds__(64 * NWM * NWN, OCC) void dgemm_lds_kernel(const Ge
         for (int jp = 0; jp < TJ / 2; ++jp)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            // element u of the pair: row i + e, column 2 jp + u (pairs_n), or row i + u, column 2 jp + e
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-              const int bi = pairs_n ? i + e : i + u, bj = pairs_n ? 2 * jp + u : 2 * jp + e;
-              const int64_t m = row(bi, r), n = col(bj);
+              const int64_t m = row(i + e, r), n = col(2 * jp + u);
               const bool ok = m < g.M && n < g.N;
               off[e][jp][r][u] = ok ? c_offset(g, m, n) : -1;
-              x[e][jp][r][u] = ok ? value(pairs_n ? acc[i + e][2 * jp + u][r] : acc[i + u][2 * jp + e][r], m, n) : 0.0;
+              x[e][jp][r][u] = ok ? value(acc[i + e][2 * jp + u][r], m, n) : 0.0;
               if (rd && ok) x[e][jp][r][u] += g.beta * C[off[e][jp][r][u]];
             }
           }
@@ -852,13 +847,13 @@ hipError_t gemm_f64(const Gemm& g0, hipStream_t s) {
   // row is one product with batch * M rows: fold it, so that it gets the large tiles.
   if (g.batch > 1 && g.sB == 0 && !g.transA && !g.upper && g.sA == g.M * g.lda && g.sC == g.M * g.ldc &&
       (!g.kscaleA || g.sksA == 0) && (!g.kscaleB || g.sksB == 0) && (!g.hmul || g.sH == g.M * g.ldh) &&
-      (!g.pair_rows || g.M % 2 == 0) && !g.xtile && g.cblk == 0 && g.ksplit == 1) {
+      !g.xtile && g.cblk == 0 && g.ksplit == 1) {
     g.M *= g.batch;
     g.batch = 1;
     g.sA = g.sC = g.sH = 0;
   }
   // Batches interleaved row by row (row m of batch b at m * batch + b) fold the same way.
-  if (g.batch > 1 && g.sB == 0 && !g.transA && !g.pair_rows && !g.upper && g.cblk == 0 && g.ksplit == 1 &&
+  if (g.batch > 1 && g.sB == 0 && !g.transA && !g.xtile && !g.upper && g.cblk == 0 && g.ksplit == 1 &&
       g.sA >= g.K &&
       g.sC >= g.N &&
       g.lda == g.batch * g.sA && g.ldc == g.batch * g.sC && (!g.kscaleA || g.sksA == 0) &&
@@ -876,8 +871,8 @@ hipError_t gemm_f64(const Gemm& g0, hipStream_t s) {
     g.K = 0;
   }
   if ((g.C == nullptr) == (g.Cf == nullptr)) return hipErrorInvalidValue;  // exactly one output
-  if ((g.xtile && !g.pair_rows) || g.cblk < 0 ||
-      (g.cblk > 0 && (g.pair_rows || (g.cblk & (g.cblk - 1)) != 0 || g.ldc % g.cblk != 0)) ||
+  if (g.cblk < 0 ||
+      (g.cblk > 0 && (g.xtile || (g.cblk & (g.cblk - 1)) != 0 || g.ldc % g.cblk != 0)) ||
       (g.upper && g.M != g.N))
     return hipErrorInvalidValue;
   // k-scale factors are read through 32-bit byte offsets
@@ -893,7 +888,7 @@ hipError_t gemm_f64(const Gemm& g0, hipStream_t s) {
       if (ns >= 2 && ns * g.batch * g.M * g.N <= g.ws_len && g.batch * ns <= 65535) {
         Gemm h = g;
         h.C = g.ws; h.ldc = g.N; h.sC = g.M * g.N; h.sSplit = g.batch * g.M * g.N;
-        h.alpha = 1.0; h.beta = 0.0; h.hmul = nullptr; h.pair_rows = false; h.xtile = false; h.cblk = 0;
+        h.alpha = 1.0; h.beta = 0.0; h.hmul = nullptr; h.xtile = false; h.cblk = 0;
         h.Cf = nullptr;
         h.ksplit = (int)ns; h.ws = nullptr;
         hipError_t e = gemm_f64(h, s);

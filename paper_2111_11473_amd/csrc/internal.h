@@ -27,9 +27,8 @@ struct Gemm {
   const double* hmul = nullptr; int64_t ldh = 0, sH = 0;
   int64_t batch = 1;
   int ksplit = 1; int64_t sSplit = 0;
-  bool pair_rows = false;  // C element (m, n) at C[((m / 2) ldc + n) 2 + m % 2]: rows interleaved in pairs
-  // With pair_rows and xtile: columns cut into tiles of 64, each tile a [ldc][64][2] block of row
-  // pairs: C[(((n / 64) ldc + m / 2) 64 + n % 64) 2 + m % 2].
+  // xtile: columns cut into tiles of 64, each a row-major [ldc][64] block:
+  // C[((n / 64) ldc + m) 64 + n % 64].
   bool xtile = false;
   // cblk > 0: C cut into 16 x cblk blocks, block-row-major, each block row-major:
   // C[((m / 16) (ldc / cblk) + n / cblk) 16 cblk + (m % 16) cblk + n % cblk] (ldc % cblk == 0).
@@ -196,23 +195,21 @@ hipError_t mlp_infer_bf16(int64_t rows, int64_t n_in, int64_t n_out, const float
                           const float* sd_in, const short* Wb, const float* bias, const float* mu_out,
                           const float* sd_out, float* Y, hipStream_t s);
 
-// VALU kernel for H^XYZ += sum_I (E^XY F^XZ + E^XZ F^XY) G^YZ (kernels_h.hip).
-// E, F: [Xb/64][ldi][Pp/2][64][2] (X tile, grid point, row pair, X within the tile, row of the
-// pair); G: [I][Pp/16][Pp/8][16][8] (16 x 8 blocks); H: [Pp][Pp][Xb]; tiles from
-// h_tiles(Pp, Xb, slots).  ldi >= nI is the grid-point stride of one X tile of E and F.  fresh:
-// H = the sum instead of H += (every element of H is written: the tiles cover all of it).
+// H^XYZ += sum_I (E^XY F^XZ + E^XZ F^XY) G^YZ (kernels_h.hip).
+// E, F: [Xb/64][ldi][Pp][64] (X tile, grid point, row, X within the tile); G: [I][Pp/16][Pp/16][16][16]
+// (16 x 16 blocks); H: [Pp][Pp][Xb]; tiles from h_tiles(Pp, Xb, slots).  ldi >= nI is the grid-point
+// stride of one X tile of E and F.  fresh: H = the sum instead of H += (every element of H is
+// written: the tiles cover all of it).
 hipError_t h_accumulate(int64_t Pp, int64_t Xb, int64_t ldi, int64_t nI, const double* E, const double* F,
                         const double* G, double* H, const uint32_t* tiles, int64_t ntiles, int64_t slots,
                         bool fresh, hipStream_t s);
-// FP32 kernel of the mixed-precision path: E, F as above in FP32; G in FP32 16 x 16 blocks,
-// [I][Pp/16][Pp/16][16][16]; FP32 arithmetic and accumulation over the chunk, added into the FP64
-// H (or written, fresh); tiles from h32_tiles (16 x 16 block pairs).
+// The same with E, F and G in FP32 (the mixed-precision path): FP32 arithmetic and accumulation over the
+// chunk, added into the FP64 H (or written, fresh); tiles from h32_tiles.
 hipError_t h_accumulate_f32(int64_t Pp, int64_t Xb, int64_t ldi, int64_t nI, const float* E, const float* F,
                             const float* G, double* H, const uint32_t* tiles, int64_t ntiles, int64_t slots,
                             bool fresh, hipStream_t s);
 std::vector<uint32_t> h32_tiles(int64_t Pp, int64_t Xb, int64_t slots);
 int64_t h32_slots_per_xcd();
-constexpr int H_GBLK = 8;  // column width of the G blocks
 std::vector<uint32_t> h_tiles(int64_t Pp, int64_t Xb, int64_t slots);
 int64_t h_slots_per_xcd();
 

@@ -1231,19 +1231,19 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
     for (int64_t X0 = 0; X0 < P; X0 += Xb) {
       const int64_t xb = std::min(Xb, P - X0);
       // C6[i][Y][x] = sum_W T[W][Y] y_i^W Gv[X][W];  D6[a][Y][x] = sum_W T[W][Y] y_a^W Go[X][W]
-      // stored [x/64][Y/2][x%64][Y%2] (X tiles of 64, row pairs interleaved: the H-kernel's layout)
+      // stored [x/64][Y][x%64] (X tiles of 64: the H-kernel's layout)
       {
-        Gemm g = batched(mk(P, xb, P, T, P, true, ctx->Gv + X0 * P, P, true, ctx->C6, Pp / 2), o, 0, 0, Xb * Pp);
-        g.kscaleA = Yo; g.ksA = 1; g.sksA = P; g.pair_rows = true; g.xtile = true;
+        Gemm g = batched(mk(P, xb, P, T, P, true, ctx->Gv + X0 * P, P, true, ctx->C6, Pp), o, 0, 0, Xb * Pp);
+        g.kscaleA = Yo; g.ksA = 1; g.sksA = P; g.xtile = true;
         RCHK(gemm(ctx, g));
-        Gemm h = batched(mk(P, xb, P, T, P, true, ctx->Go + X0 * P, P, true, ctx->D6, Pp / 2), v, 0, 0, Xb * Pp);
-        h.kscaleA = Yv; h.ksA = 1; h.sksA = P; h.pair_rows = true; h.xtile = true;
+        Gemm h = batched(mk(P, xb, P, T, P, true, ctx->Go + X0 * P, P, true, ctx->D6, Pp), v, 0, 0, Xb * Pp);
+        h.kscaleA = Yv; h.ksA = 1; h.sksA = P; h.xtile = true;
         RCHK(gemm(ctx, h));
       }
       for (int64_t I0 = 0; I0 < Q; I0 += ctx->Ic) {
         const int64_t ic = std::min(ctx->Ic, Q - I0);
         // E_I = sum_i x_i^I C6[i];  F_I = sum_a x_a^I D6[a], one product per X tile, stored
-        // [x/64][I][Y/2][x%64][Y%2] (a tile's rows for consecutive I are adjacent)
+        // [x/64][I][Y][x%64] (a tile's rows for consecutive I are adjacent)
         {
           const int64_t tb = Pp * 64;  // elements of one X tile of C6[i], D6[a], E_I, F_I
           Gemm ge = batched(mk(ic, tb, o, xo + I0, Q, true, ctx->C6, Xb * Pp, false, ctx->Ec, tb), nX, 0, tb, ctx->Ic * tb);
@@ -1255,17 +1255,12 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
           RCHK(gemm(ctx, ge));
           RCHK(gemm(ctx, gf));
         }
-        // G_I[Y][Z] = sum_ia y_i^Y y_a^Z B_ia^I   (Alg. 6), stored in 16 x H_GBLK blocks (FP64) or
-        // in 16 x 16 blocks (FP32, mixed precision)
+        // G_I[Y][Z] = sum_ia y_i^Y y_a^Z B_ia^I   (Alg. 6), stored in 16 x 16 blocks
         RCHK(gemm(ctx, mk(ic * o, P, v, ctx->Bq + I0 * ov, v, false, Yv, P, false, ctx->GYc, P)));
-        if (ctx->mixed) {
-          Gemm gg = batched(mk(P, P, o, Yo, P, true, ctx->GYc, P, false, nullptr, Pp), ic, 0, o * P, Pp * Pp);
-          gg.Cf = ctx->G32;
-          gg.cblk = 16;
-          RCHK(gemm(ctx, gg));
-        } else {
+        {
           Gemm gg = batched(mk(P, P, o, Yo, P, true, ctx->GYc, P, false, ctx->Gc, Pp), ic, 0, o * P, Pp * Pp);
-          gg.cblk = H_GBLK;
+          gg.cblk = 16;
+          if (ctx->mixed) { gg.C = nullptr; gg.Cf = ctx->G32; }
           RCHK(gemm(ctx, gg));
         }
         if (ctx->mixed) {

@@ -1,0 +1,56 @@
+"""The H-kernel (Alg. 6's three-way accumulation) at the edges of its tiles and of its copy pipeline: ranks one
+below, at and one above the 16-row blocks and 64-wide X tiles, chunks of fewer, as many and a few more
+grid points than stages, several X blocks -- Eq. 32 + 33 against the dense oracle in FP64 and in mixed precision."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from paper_2111_11473_amd import synth
+from test_gpu_parity import RTOL_TERM, _dev, _host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def thc():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2111_11473_amd import thc as mod
+    mod.load()
+    return mod
+
+
+# (nP, nQ, grid points per chunk, X block); 0: the planner's choice
+CASES = [(1, 3, 0, 0), (15, 17, 1, 0), (16, 21, 2, 0), (17, 20, 3, 0), (31, 25, 4, 0), (33, 23, 5, 0), (63, 30, 7, 0),
+         (64, 29, 8, 0), (65, 33, 9, 64), (80, 41, 11, 64), (129, 45, 0, 128)]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("P,Q,i_chunk,x_block", CASES)
+def test_alg6_at_edges(thc, P, Q, i_chunk, x_block, precision):
+    print(f"[gpu-hkernel] nP {P} nQ {Q} i_chunk {i_chunk} x_block {x_block} precision {precision}", flush=True)
+    o, v = 6, 25
+    rng = np.random.default_rng(100 * P + Q)
+    n, nL = o + v, 40
+    eps = np.concatenate([np.sort(rng.uniform(-1.5, -0.3, o)), np.sort(rng.uniform(0.1, 5.0, v))])
+    L = rng.standard_normal((nL, n, n))
+    L = 0.02 * (L + L.transpose(0, 2, 1))
+    Xo, Xv, xo, xv = (rng.standard_normal((m, r)) / np.sqrt(r) for m, r in ((o, P), (v, P), (o, Q), (v, Q)))
+    ctx = thc.THC(o, v, nL, P, Q, precision=precision, i_chunk=i_chunk, x_block=x_block, flags=thc.FLAG_QUARTIC)
+    ctx.build_factors(*map(_dev, (L, eps, Xo, Xv, xo, xv)))
+    if i_chunk:
+        assert ctx.plan()["i_chunk"] == i_chunk
+    R = rng.standard_normal((P, P))
+    Z, t1 = R + R.T, 0.02 * rng.standard_normal((o, v))
+    z, _ = oracle.eri_fit(L, o, xo, xv)
+    ref, _ = oracle.thc_residual(eps, L, Xo, Xv, Z, t1, oracle.eri_thc_dense(xo, xv, z), terms=True)
+    want = ref["eq32"] + ref["eq33"]
+    for _ in range(2):  # the second pass finds the first one's H and operands in place
+        got, _ = ctx.residual(_dev(Z), _dev(t1), mask=thc.TERM_EQ32)
+        err = np.abs(_host(got) - want).max() / np.abs(want).max()
+        # FP64: the bound of every term.  FP32 operands, products and chunk sums: about ten roundings of 6e-8 a
+        # factor chain and sums of cancelling terms -- the mixed path's bound
+        assert err < (RTOL_TERM if precision == 0 else 5e-5), err
+    ctx.close()
