@@ -667,16 +667,14 @@ std::vector<BufSpec> quintic_list(thc_ctx* ctx) {
           {&ctx->qI1, (size_t)(n * w * P)}};
 }
 
-// Picks the blocking (nb, KS, Xb, Ic, X7, the residency of the vv block) for a budget of device
-// bytes and fills ctx->plan_bytes; THC_ENOMEM if even the smallest blocking does not fit.
-int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
+// Picks the blocking (KS, Xb, Ic, X7, the residency of the vv block) for fused-pass blocks of nb vectors and
+// a budget of device bytes; THC_ENOMEM if even the smallest blocking does not fit.
+int plan_with_block(thc_ctx* ctx, double budget, int64_t slots, int64_t nb) {
   const int64_t o = ctx->o, v = ctx->v, nL = ctx->nL, P = ctx->P, Q = ctx->Q, ov = ctx->ov;
   const int64_t Pp = ctx->Pp = ((P + 15) / 16) * 16;  // Y, Z ranks of H padded to its 16-wide blocks
   const int64_t P64 = ((P + 63) / 64) * 64;           // X ranks padded to its 64-lane tiles
   const thc_options& op = ctx->opt;
-  // fused-pass block: four nb x P^2 panels within ~4 GB
-  int64_t nb = op.a_block > 0 ? op.a_block : std::max<int64_t>(1, std::min<int64_t>(64, (int64_t)(4.0e9 / (32.0 * P * P))));
-  ctx->nb = nb = std::min(nb, nL);
+  ctx->nb = nb;
   // split of the N_L P-deep sum of Alg. 1: at most 512 workgroups of 128 x 128 tiles (one round
   // at two per CU), counting the tiles on and above the diagonal (the product is symmetric)
   const int64_t nt128 = (P + 127) / 128, t128 = nt128 * (nt128 + 1) / 2;
@@ -766,6 +764,39 @@ int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
   if (Ic <= 0) Ic = std::max<int64_t>(1, (int64_t)(std::min(rem, std::max(16.0e9, 256.0 * per_i(Xb))) / per_i(Xb)));
   ctx->Ic = std::min(Ic, Q);
   return THC_OK;
+}
+
+// Device bytes of the plan in ctx.
+double plan_bytes(thc_ctx* ctx, int64_t slots) {
+  const double r6 = list_bytes(ctx->quintic ? quintic_list(ctx) : region6_list(ctx));
+  return list_bytes(persistent_list(ctx)) +
+         8.0 * (double)tile_table_doubles(ctx->Pp, ctx->Xb, slots) * (ctx->opt.precision >= 1 ? 2.0 : 1.0) +
+         std::max(r6, 8.0 * (double)setup_doubles(ctx)) + list_bytes(alg7_list(ctx));
+}
+
+// The fused-pass block: four nb x P^2 panels within ~4 GB and at most 64 Cholesky vectors or, where the
+// panels stay no larger than they are at P = 1000 with 64 (64e6 values), as many as that allows in blocks of
+// equal length: the pass is some 75 launches a block, so small ranks want few blocks and middling ones
+// products over many vectors.  Residual at P = 50, nL = 70: 1.05 ms in blocks of 64, 0.85 in one; P = 620,
+// nL = 930: 111.2 ms in blocks of 64, 104.0 of 155; a solve at P = 120:
+// 14.0 -> 10.1 ms.  Mixed precision keeps 64, which its FP32 sums over vectors and their splits follow.  The longer block is taken only where the budget leaves the rest of the plan as it is.
+int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
+  const int64_t nL = ctx->nL, P = ctx->P, n2 = std::max(std::max(P, ctx->o), ctx->v);
+  int64_t nb = ctx->opt.a_block > 0 ? ctx->opt.a_block : std::max<int64_t>(1, std::min<int64_t>(64, (int64_t)(4.0e9 / (32.0 * P * P))));
+  nb = std::min(nb, nL);
+  const int rc = plan_with_block(ctx, budget, slots, nb);
+  const int64_t most = std::min<int64_t>(1024, (int64_t)(64.0e6 / ((double)n2 * n2)));
+  if (rc != THC_OK || ctx->opt.a_block > 0 || ctx->opt.precision >= 1 || most <= nb || nb == nL) return rc;
+  const int64_t blocks = (nL + most - 1) / most;
+  const int64_t longer = (nL + blocks - 1) / blocks;
+  const int64_t Xb = ctx->Xb, Ic = ctx->Ic, X7 = ctx->X7, nq = ctx->nq, jq = ctx->jq;
+  const bool resident = ctx->lvv_resident;
+  if (longer <= nb) return rc;
+  if (plan_with_block(ctx, budget, slots, longer) == THC_OK && ctx->Xb == Xb && ctx->Ic == Ic && ctx->X7 == X7 &&
+      ctx->nq == nq && ctx->jq == jq && ctx->lvv_resident == resident && plan_bytes(ctx, slots) <= budget)
+    return THC_OK;
+  ctx->err.clear();
+  return plan_with_block(ctx, budget, slots, nb);
 }
 
 // The plan for the context's budget (its workspace, else the device's free memory up to
@@ -1634,15 +1665,9 @@ int thc_plan_query(const thc_options* opt, int synthetic, uint64_t budget_bytes,
   }
   const int rc = choose_plan(&c, (double)budget_bytes, slots);
   if (rc != THC_OK) return rc;
-  const double pers = list_bytes(persistent_list(&c)),
-               r6 = list_bytes(c.quintic ? quintic_list(&c) : region6_list(&c));
-  const double a7 = list_bytes(alg7_list(&c)), setup = 8.0 * (double)setup_doubles(&c);
   int64_t tiles = 0, entries = 0;
   tile_counts(c.Pp, c.Xb, slots, &tiles, &entries);
-  fill_plan_info(&c, tiles, entries, slots,
-                 pers + 8.0 * (double)tile_table_doubles(c.Pp, c.Xb, slots) * (opt->precision >= 1 ? 2.0 : 1.0) +
-                     std::max(r6, setup) + a7,
-                 out);
+  fill_plan_info(&c, tiles, entries, slots, plan_bytes(&c, slots), out);
   return THC_OK;
 }
 
