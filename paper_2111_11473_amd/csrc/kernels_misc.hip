@@ -29,24 +29,51 @@ __device__ double block_sum(double x) {
   return r;
 }
 
+// Sums over the Cholesky vectors of a block, one output element a thread, have too few threads for the chip
+// when the elements are few and each walks its vectors one load after the other.  SL slices of the vectors then
+// share an element, their sums added through LDS: SL = 8 below SLICE_LEN elements (four waves a SIMD), 1
+// above, where the elements alone fill the device.  A residual at P = 120 (nL = 150): 1.49 -> 1.24 ms, at
+// P = 400 (nL = 600): 23.2 -> 22.4.
+constexpr int64_t SLICE_LEN = 262144;
+template <int SL>
+__device__ inline double slice_sum(double s, int sl, double (&part)[SL][TPB / SL]) {
+  if constexpr (SL > 1) {
+    const int c = threadIdx.x % (TPB / SL);
+    __syncthreads();  // the sums of the element before are read
+    part[sl][c] = s;
+    __syncthreads();
+    s = 0.0;
+    for (int k = 0; k < SL; ++k) s += part[k][c];
+  }
+  return s;
+}
+
 // The Hadamard steps of Alg. 1 and Alg. 3 fused: for the nb Cholesky vectors of a block,
 // C^A = Go o Bvv^A - Gv o Boo^A written in the [X][A][Y] layout that the C T C^T chain
 // reads, and C3 += sum_A Boo^A o Bvv^A.
+template <int SL>
 __global__ void form_C_kernel(int64_t P, int64_t nb, const double* __restrict__ Bvv,
                               const double* __restrict__ Boo, const double* __restrict__ Go,
                               const double* __restrict__ Gv, double* __restrict__ Ccat,
                               double* __restrict__ C3) {
   const int64_t PP = P * P;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < PP; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t X = e / P, Y = e % P;
-    const double go = Go[e], gv = Gv[e];
+  const int sl = threadIdx.x / (TPB / SL);
+  __shared__ double part[SL][TPB / SL];
+  for (int64_t e0 = (int64_t)blockIdx.x * (TPB / SL); e0 < PP; e0 += (int64_t)gridDim.x * (TPB / SL)) {
+    const int64_t e = e0 + threadIdx.x % (TPB / SL);
     double c3 = 0.0;
-    for (int64_t A = 0; A < nb; ++A) {
-      const double bv = Bvv[A * PP + e], bo = Boo[A * PP + e];
-      Ccat[X * nb * P + A * P + Y] = go * bv - gv * bo;
-      c3 += bo * bv;
+    if (e < PP) {
+      const int64_t X = e / P, Y = e % P;
+      const double go = Go[e], gv = Gv[e];
+#pragma unroll 4
+      for (int64_t A = sl; A < nb; A += SL) {
+        const double bv = Bvv[A * PP + e], bo = Boo[A * PP + e];
+        Ccat[X * nb * P + A * P + Y] = go * bv - gv * bo;
+        c3 += bo * bv;
+      }
     }
-    C3[e] += c3;
+    c3 = slice_sum<SL>(c3, sl, part);
+    if (sl == 0 && e < PP) C3[e] += c3;
   }
 }
 
@@ -107,15 +134,6 @@ __global__ __launch_bounds__(TPB) void hadamard_energy_kernel(int64_t P, const d
   if (threadIdx.x == 0) epart[A * gridDim.x + blockIdx.x] = s;
 }
 
-__global__ void batch_sum_kernel(int64_t nb, int64_t len, const double* __restrict__ X, double alpha,
-                                 double* __restrict__ out) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < len; e += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0.0;
-    for (int64_t A = 0; A < nb; ++A) s += X[A * len + e];
-    out[e] += alpha * s;
-  }
-}
-
 __global__ void batch_sum_sym_kernel(int64_t nb, int64_t P, const double* __restrict__ X, double alpha,
                                      double* __restrict__ out) {
   const int64_t PP = P * P;
@@ -128,12 +146,20 @@ __global__ void batch_sum_sym_kernel(int64_t nb, int64_t P, const double* __rest
   }
 }
 
+// out[e] += alpha sum_A w[A] X[A][e] (w null: 1)
+template <int SL, bool W>
 __global__ void wsum_kernel(int64_t nb, int64_t len, const double* __restrict__ w, const double* __restrict__ X,
                             int64_t sX, double alpha, double* __restrict__ out) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < len; e += (int64_t)gridDim.x * blockDim.x) {
+  const int sl = threadIdx.x / (TPB / SL);
+  __shared__ double part[SL][TPB / SL];
+  for (int64_t e0 = (int64_t)blockIdx.x * (TPB / SL); e0 < len; e0 += (int64_t)gridDim.x * (TPB / SL)) {
+    const int64_t e = e0 + threadIdx.x % (TPB / SL);
     double s = 0.0;
-    for (int64_t A = 0; A < nb; ++A) s += w[A] * X[A * sX + e];
-    out[e] += alpha * s;
+    if (e < len)
+#pragma unroll 4
+      for (int64_t A = sl; A < nb; A += SL) s += W ? w[A] * X[A * sX + e] : X[A * sX + e];
+    s = slice_sum<SL>(s, sl, part);
+    if (sl == 0 && e < len) out[e] += alpha * s;
   }
 }
 
@@ -354,7 +380,8 @@ __global__ void set_diag_kernel(int64_t n, const double* __restrict__ d, double*
 
 hipError_t k_form_C(int64_t P, int64_t nb, const double* Bvv, const double* Boo, const double* Go, const double* Gv,
                     double* Ccat, double* C3, hipStream_t s) {
-  LAUNCH(form_C_kernel, dim3(nblocks(P * P)), dim3(TPB), P, nb, Bvv, Boo, Go, Gv, Ccat, C3);
+  if (P * P < SLICE_LEN) LAUNCH(form_C_kernel<8>, dim3(nblocks(8 * P * P)), dim3(TPB), P, nb, Bvv, Boo, Go, Gv, Ccat, C3);
+  LAUNCH(form_C_kernel<1>, dim3(nblocks(P * P)), dim3(TPB), P, nb, Bvv, Boo, Go, Gv, Ccat, C3);
 }
 hipError_t k_colsum_rowscaled(int64_t nb, int64_t rows, int64_t P, const double* Y, const double* W, int64_t sW,
                               double* out, int64_t ldo, hipStream_t s) {
@@ -366,14 +393,16 @@ hipError_t k_hadamard_energy(int64_t P, int64_t nb, const double* T, const doubl
   LAUNCH(hadamard_energy_kernel, dim3(64, (unsigned)nb), dim3(TPB), P, T, MT, F, epart);
 }
 hipError_t k_batch_sum(int64_t nb, int64_t len, const double* X, double alpha, double* out, hipStream_t s) {
-  LAUNCH(batch_sum_kernel, dim3(nblocks(len)), dim3(TPB), nb, len, X, alpha, out);
+  if (len < SLICE_LEN) LAUNCH((wsum_kernel<8, false>), dim3(nblocks(8 * len)), dim3(TPB), nb, len, nullptr, X, len, alpha, out);
+  LAUNCH((wsum_kernel<1, false>), dim3(nblocks(len)), dim3(TPB), nb, len, nullptr, X, len, alpha, out);
 }
 hipError_t k_batch_sum_sym(int64_t nb, int64_t P, const double* X, double alpha, double* out, hipStream_t s) {
   LAUNCH(batch_sum_sym_kernel, dim3(nblocks(P * P)), dim3(TPB), nb, P, X, alpha, out);
 }
 hipError_t k_wsum(int64_t nb, int64_t len, const double* w, const double* X, int64_t sX, double alpha, double* out,
                   hipStream_t s) {
-  LAUNCH(wsum_kernel, dim3(nblocks(len)), dim3(TPB), nb, len, w, X, sX, alpha, out);
+  if (len < SLICE_LEN) LAUNCH((wsum_kernel<8, true>), dim3(nblocks(8 * len)), dim3(TPB), nb, len, w, X, sX, alpha, out);
+  LAUNCH((wsum_kernel<1, true>), dim3(nblocks(len)), dim3(TPB), nb, len, w, X, sX, alpha, out);
 }
 hipError_t k_copy2d(int64_t batch, int64_t rows, int64_t cols, const double* src, int64_t lds, int64_t sbs,
                     double* dst, int64_t ldd, int64_t sbd, bool transpose, hipStream_t s) {
