@@ -199,9 +199,15 @@ hipError_t mlp_infer_bf16(int64_t rows, int64_t n_in, int64_t n_out, const float
 // E, F: [Xb/64][ldi][Pp][64] (X tile, grid point, row, X within the tile); G: [I][Pp/16][Pp/16][16][16]
 // (16 x 16 blocks); H: [Pp][Pp][Xb]; tiles from h_tiles(Pp, Xb, slots).  ldi >= nI is the grid-point
 // stride of one X tile of E and F.  fresh: H = the sum instead of H += (every element of H is
-// written: the tiles cover all of it).
+// written: the tiles cover all of it).  slices > 1: slice s of the grid points goes to H + s Pp Pp Xb.
+constexpr int H_SLICES = 8;
+// Tiles per run of the table (its `slots`): the device's slots per XCD, or an eighth of the tiles where they are
+// fewer than one generation -- full runs would leave them to the first XCDs alone.
+int64_t h_run_length(int64_t Pp, int64_t Xb, int64_t slots);
+int64_t h32_run_length(int64_t Pp, int64_t Xb, int64_t slots);
+int h_slices(int64_t Pp, int64_t Xb, int64_t nI, int64_t slots);
 hipError_t h_accumulate(int64_t Pp, int64_t Xb, int64_t ldi, int64_t nI, const double* E, const double* F,
-                        const double* G, double* H, const uint32_t* tiles, int64_t ntiles, int64_t slots,
+                        const double* G, double* H, const uint32_t* tiles, int64_t ntiles, int64_t slots, int slices,
                         bool fresh, hipStream_t s);
 // The same with E, F and G in FP32 (the mixed-precision path): FP32 arithmetic and accumulation over the
 // chunk, added into the FP64 H (or written, fresh); tiles from h32_tiles.

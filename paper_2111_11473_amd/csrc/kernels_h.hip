@@ -303,7 +303,7 @@ struct Patch<float> {
 };
 
 template <typename T>
-__global__ __launch_bounds__(256, 2) void h_kernel(int Pp, int Xb, int64_t ldi, int64_t nI, const T* __restrict__ E,
+__global__ __launch_bounds__(256, 2) void h_kernel(int Pp, int Xb, int64_t ldi, int64_t nIall, const T* __restrict__ E,
                                                    const T* __restrict__ F, const T* __restrict__ G,
                                                    double* __restrict__ H, const uint32_t* __restrict__ tiles,
                                                    int flags) {
@@ -329,6 +329,9 @@ __global__ __launch_bounds__(256, 2) void h_kernel(int Pp, int Xb, int64_t ldi, 
 
   Patch<T> p;
   p.offsets(lane, w);
+  // this slice's grid points and its H (gridDim.y slices)
+  const int64_t I0 = nIall * blockIdx.y / gridDim.y, nI = nIall * (blockIdx.y + 1) / gridDim.y - I0;
+  H += (int64_t)blockIdx.y * Pp * Pp * Xb;
   // lane's element (Y, Z, X) of H and of its mirror
   const int Z = z0 + (lane & 15), X0 = xt * XT + zs * C::XW + Patch<T>::x_of(w);
   auto at = [&](bool m, int r) {
@@ -369,7 +372,7 @@ __global__ __launch_bounds__(256, 2) void h_kernel(int Pp, int Xb, int64_t ldi, 
   const int64_t PP = (int64_t)Pp * Pp;  // elements of G per I
   // Sources of the next stage to copy: a generation walks the grid points forwards or (rev)
   // backwards, so each stage moves the three pointers by one grid point.
-  const int64_t first = (rev && nI > 0) ? nI - 1 : 0;
+  const int64_t first = I0 + ((rev && nI > 0) ? nI - 1 : 0);
   const T* e_at = E + ((int64_t)xt * ldi + first) * PX;
   const T* f_at = F + ((int64_t)xt * ldi + first) * PX;
   const T* g_at = G + first * PP;
@@ -403,10 +406,10 @@ __global__ __launch_bounds__(256, 2) void h_kernel(int Pp, int Xb, int64_t ldi, 
     p.point(lds + buf * C::STAGE_B);
     __builtin_amdgcn_sched_barrier(0);
   };
-  // The two workgroups of a CU (ids half a generation apart) take the higher wave priority in turn, two
-  // grid points each.  Left at equal priority the older one always wins: it ran a 300-point tile in 193 us and
-  // the other, alone at the end with one wave per SIMD, in 287 us; in turn both take 255 us.
-  const int later_half = blockIdx.x >= gridDim.x / 2;
+  // The two workgroups of a CU (ids 256 apart, one round of the device's CUs) take the higher wave priority in
+  // turn, two grid points each.  Left at equal priority the older one always wins: it ran a 300-point tile in
+  // 193 us and the other, alone at the end with one wave per SIMD, in 287 us; in turn both take 255 us.
+  const int odd_round = ((blockIdx.x + gridDim.x * blockIdx.y) >> 8) & 1;
   // Steady state: every grid point also issues the stage D ahead, and the stage after the next
   // one (D - 1 of them) may stay in flight.  NS points a turn, so that buffers are constants.
   const int64_t steady = nI - D;
@@ -414,7 +417,7 @@ __global__ __launch_bounds__(256, 2) void h_kernel(int Pp, int Xb, int64_t ldi, 
   for (; I + NS <= steady; I += NS)
 #pragma unroll
     for (int b = 0; b < NS; ++b) {
-      if (((b >> 1) ^ later_half) & 1) __builtin_amdgcn_s_setprio(2);
+      if (((b >> 1) ^ odd_round) & 1) __builtin_amdgcn_s_setprio(2);
       else __builtin_amdgcn_s_setprio(1);
       stage_in((b + D) % NS);
       consume(b);
@@ -495,16 +498,16 @@ std::vector<uint32_t> tiles_for(int64_t Pp, int64_t Xb, int64_t slots) {
 
 template <typename T>
 hipError_t launch(int64_t Pp, int64_t Xb, int64_t ldi, int64_t nI, const T* E, const T* F, const T* G, double* H,
-                  const uint32_t* tiles, int64_t ntiles, int64_t slots, bool fresh, hipStream_t s) {
+                  const uint32_t* tiles, int64_t ntiles, int64_t slots, int slices, bool fresh, hipStream_t s) {
   if (Pp % BY != 0 || Pp <= 0 || Pp > 8192 || Xb % XT != 0 || Xb > (Pp + XT - 1) / XT * XT || Xb <= 0 || ntiles <= 0 || ntiles > 2147483647LL ||
-      nI < 0 || ldi < nI || slots < 1 || ntiles % (8 * slots) != 0)
+      nI < 0 || ldi < nI || slots < 1 || ntiles % (8 * slots) != 0 || slices < 1 || slices > H_SLICES)
     return hipErrorInvalidValue;
   // One launch per generation of 8 slots tiles (every workgroup resident at once): the runs of
   // a generation start together, so the workgroups sharing operand rows through an L2 stay
   // within one tile's lifetime of each other.
   const int64_t gen = 8 * slots;
   for (int64_t t0 = 0; t0 < ntiles; t0 += gen) {
-    hipLaunchKernelGGL(h_kernel<T>, dim3((unsigned)gen), dim3(256), 0, s, (int)Pp, (int)Xb, ldi, nI, E, F, G, H,
+    hipLaunchKernelGGL(h_kernel<T>, dim3((unsigned)gen, (unsigned)slices), dim3(256), 0, s, (int)Pp, (int)Xb, ldi, nI, E, F, G, H,
                        tiles + t0, (int)((t0 / gen) & 1) | (fresh ? 2 : 0));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -523,9 +526,26 @@ int64_t slots_per_xcd() {
   return std::max<int64_t>(1, (int64_t)(cus / 8) * std::max(per_cu, 1));
 }
 
+int64_t h_run(int64_t Pp, int64_t Xb, int64_t slots, int nzs) {
+  const int64_t nB = Pp / BY, tiles = nB * (nB + 1) / 2 * nzs * (Xb / XT);
+  return std::min(slots, std::max<int64_t>(1, (tiles + 7) / 8));
+}
+
 }  // namespace
 
 int64_t h_slots_per_xcd() { return slots_per_xcd<double>(); }
+
+int64_t h_run_length(int64_t Pp, int64_t Xb, int64_t slots) { return h_run(Pp, Xb, slots, Geo<double>::NZS); }
+int64_t h32_run_length(int64_t Pp, int64_t Xb, int64_t slots) { return h_run(Pp, Xb, slots, Geo<float>::NZS); }
+
+// Slices of the grid points, each with its own H, that fill the device's 8 slots tiles where the ranks have
+// too few (the caller adds the slices up): one workgroup's walk over the points is a serial chain.  At least 16
+// points each.  With even runs (h_run_length), a solve at P = 120 (144 tiles, 300 points): 8.7 -> 7.9 ms, a residual
+// at P = 50 (20 tiles, 110 points): 0.755 -> 0.717.
+int h_slices(int64_t Pp, int64_t Xb, int64_t nI, int64_t slots) {
+  const int64_t nB = Pp / BY, tiles = nB * (nB + 1) / 2 * Geo<double>::NZS * (Xb / XT);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({8 * slots / tiles, nI / 16, H_SLICES}));
+}
 
 // Tile table: every (X tile, Y block Yb, Z block Zb >= Yb, slice of X) once, in runs of `slots`
 // tiles that share an X tile and a Hilbert-curve patch of block pairs; run c sits at workgroup ids
@@ -534,9 +554,9 @@ int64_t h_slots_per_xcd() { return slots_per_xcd<double>(); }
 std::vector<uint32_t> h_tiles(int64_t Pp, int64_t Xb, int64_t slots) { return tiles_for<Geo<double>::NZS>(Pp, Xb, slots); }
 
 hipError_t h_accumulate(int64_t Pp, int64_t Xb, int64_t ldi, int64_t nI, const double* E, const double* F,
-                        const double* G, double* H, const uint32_t* tiles, int64_t ntiles, int64_t slots,
+                        const double* G, double* H, const uint32_t* tiles, int64_t ntiles, int64_t slots, int slices,
                         bool fresh, hipStream_t s) {
-  return launch<double>(Pp, Xb, ldi, nI, E, F, G, H, tiles, ntiles, slots, fresh, s);
+  return launch<double>(Pp, Xb, ldi, nI, E, F, G, H, tiles, ntiles, slots, slices, fresh, s);
 }
 
 int64_t h32_slots_per_xcd() { return slots_per_xcd<float>(); }
@@ -546,7 +566,7 @@ std::vector<uint32_t> h32_tiles(int64_t Pp, int64_t Xb, int64_t slots) { return 
 hipError_t h_accumulate_f32(int64_t Pp, int64_t Xb, int64_t ldi, int64_t nI, const float* E, const float* F,
                             const float* G, double* H, const uint32_t* tiles, int64_t ntiles, int64_t slots,
                             bool fresh, hipStream_t s) {
-  return launch<float>(Pp, Xb, ldi, nI, E, F, G, H, tiles, ntiles, slots, fresh, s);
+  return launch<float>(Pp, Xb, ldi, nI, E, F, G, H, tiles, ntiles, slots, 1, fresh, s);
 }
 
 }  // namespace thc

@@ -56,6 +56,7 @@ struct thc_ctx {
   double gamma = 0.0;         // global scale of the Cholesky vectors in use
   bool lvv_resident = true;   // the vv Cholesky block is held; else regenerated per fused-pass block
   int64_t nb = 0, KS = 1, Xb = 0, Ic = 0, Xc = 0, X7 = 0;
+  int hslices = 1;  // slices of the grid points in the FP64 H-kernel, each with its own H
 
   std::vector<void*> allocs;
   size_t arena_bytes = 0;  // length of the library-allocated arena (0: the caller's workspace)
@@ -592,7 +593,7 @@ std::vector<BufSpec> region6_list(thc_ctx* ctx) {
   std::vector<BufSpec> l = {
       {&ctx->C6, (size_t)(o * Xb * Pp)}, {&ctx->D6, (size_t)(v * Xb * Pp)}, {&ctx->Ec, (size_t)(Ic * Xb * Pp)},
       {&ctx->Fc, (size_t)(Ic * Xb * Pp)}, {&ctx->Gc, (size_t)(Ic * Pp * Pp)}, {&ctx->GYc, (size_t)(Ic * o * P)},
-      {&ctx->Hb, (size_t)(Xb * Pp * Pp)}, {&ctx->R1, (size_t)(Xb * Pp * o)}, {&ctx->I6, (size_t)(Xb * ov)}};
+      {&ctx->Hb, (size_t)(ctx->hslices * Xb * Pp * Pp)}, {&ctx->R1, (size_t)(Xb * Pp * o)}, {&ctx->I6, (size_t)(Xb * ov)}};
   return l;
 }
 
@@ -667,6 +668,14 @@ std::vector<BufSpec> quintic_list(thc_ctx* ctx) {
           {&ctx->qI1, (size_t)(n * w * P)}};
 }
 
+// Device bytes of the plan in ctx.
+double plan_bytes(thc_ctx* ctx, int64_t slots) {
+  const double r6 = list_bytes(ctx->quintic ? quintic_list(ctx) : region6_list(ctx));
+  return list_bytes(persistent_list(ctx)) +
+         8.0 * (double)tile_table_doubles(ctx->Pp, ctx->Xb, slots) * (ctx->opt.precision >= 1 ? 2.0 : 1.0) +
+         std::max(r6, 8.0 * (double)setup_doubles(ctx)) + list_bytes(alg7_list(ctx));
+}
+
 // Picks the blocking (KS, Xb, Ic, X7, the residency of the vv block) for fused-pass blocks of nb vectors and
 // a budget of device bytes; THC_ENOMEM if even the smallest blocking does not fit.
 int plan_with_block(thc_ctx* ctx, double budget, int64_t slots, int64_t nb) {
@@ -675,6 +684,7 @@ int plan_with_block(thc_ctx* ctx, double budget, int64_t slots, int64_t nb) {
   const int64_t P64 = ((P + 63) / 64) * 64;           // X ranks padded to its 64-lane tiles
   const thc_options& op = ctx->opt;
   ctx->nb = nb;
+  ctx->hslices = 1;
   // split of the N_L P-deep sum of Alg. 1: at most 512 workgroups of 128 x 128 tiles (one round
   // at two per CU), counting the tiles on and above the diagonal (the product is symmetric)
   const int64_t nt128 = (P + 127) / 128, t128 = nt128 * (nt128 + 1) / 2;
@@ -763,15 +773,12 @@ int plan_with_block(thc_ctx* ctx, double budget, int64_t slots, int64_t nb) {
   int64_t Ic = op.i_chunk;
   if (Ic <= 0) Ic = std::max<int64_t>(1, (int64_t)(std::min(rem, std::max(16.0e9, 256.0 * per_i(Xb))) / per_i(Xb)));
   ctx->Ic = std::min(Ic, Q);
+  // further H blocks for slices of the grid points, from what is left
+  const double hbytes = 8.0 * (double)aligned((size_t)(Xb * Pp * Pp));
+  const double spare = (rem - per_i(Xb) * (double)ctx->Ic) / hbytes;
+  ctx->hslices = std::min(h_slices(Pp, Xb, ctx->Ic, slots), 1 + (int)std::max(0.0, std::min(spare, (double)H_SLICES)));
+  if (plan_bytes(ctx, slots) > budget) ctx->hslices = 1;
   return THC_OK;
-}
-
-// Device bytes of the plan in ctx.
-double plan_bytes(thc_ctx* ctx, int64_t slots) {
-  const double r6 = list_bytes(ctx->quintic ? quintic_list(ctx) : region6_list(ctx));
-  return list_bytes(persistent_list(ctx)) +
-         8.0 * (double)tile_table_doubles(ctx->Pp, ctx->Xb, slots) * (ctx->opt.precision >= 1 ? 2.0 : 1.0) +
-         std::max(r6, 8.0 * (double)setup_doubles(ctx)) + list_bytes(alg7_list(ctx));
 }
 
 // The fused-pass block: four nb x P^2 panels within ~4 GB and at most 64 Cholesky vectors or, where the
@@ -791,9 +798,10 @@ int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
   const int64_t longer = (nL + blocks - 1) / blocks;
   const int64_t Xb = ctx->Xb, Ic = ctx->Ic, X7 = ctx->X7, nq = ctx->nq, jq = ctx->jq;
   const bool resident = ctx->lvv_resident;
+  const int hslices = ctx->hslices;
   if (longer <= nb) return rc;
   if (plan_with_block(ctx, budget, slots, longer) == THC_OK && ctx->Xb == Xb && ctx->Ic == Ic && ctx->X7 == X7 &&
-      ctx->nq == nq && ctx->jq == jq && ctx->lvv_resident == resident && plan_bytes(ctx, slots) <= budget)
+      ctx->nq == nq && ctx->jq == jq && ctx->lvv_resident == resident && ctx->hslices == hslices && plan_bytes(ctx, slots) <= budget)
     return THC_OK;
   ctx->err.clear();
   return plan_with_block(ctx, budget, slots, nb);
@@ -874,11 +882,13 @@ int plan_and_alloc(thc_ctx* ctx) {
     budget = std::min(MEM_CAP, (double)freeb + (double)kept.bytes - 2.0e9);
   }
   RCHK(choose_plan(ctx, budget, ctx->hslots));
+  ctx->hslots = h_run_length(ctx->Pp, ctx->Xb, ctx->hslots);
   const std::vector<uint32_t> tiles = h_tiles(ctx->Pp, ctx->Xb, ctx->hslots);
   std::vector<uint32_t> tiles32;
   if (ctx->opt.precision >= 1 && !ctx->quintic) {
     ctx->hslots32 = h32_slots_per_xcd();
     if (ctx->hslots32 < 1) { ctx->err = "cannot query the device for the H-kernel launch"; return THC_EDEVICE; }
+    ctx->hslots32 = h32_run_length(ctx->Pp, ctx->Xb, ctx->hslots32);
     tiles32 = h32_tiles(ctx->Pp, ctx->Xb, ctx->hslots32);
   }
   double* tb = nullptr;
@@ -1303,9 +1313,11 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
           Scope sc(ctx, "h_kernel");
           sc.launches = ctx->nhtiles / (8 * ctx->hslots);  // one dispatch per generation of tiles
           HIPCHK(h_accumulate(Pp, Xb, ctx->Ic, ic, ctx->Ec, ctx->Fc, ctx->Gc, ctx->Hb, ctx->htiles, ctx->nhtiles,
-                              ctx->hslots, I0 == 0, s));
+                              ctx->hslots, ctx->hslices, I0 == 0, s));
         }
       }
+      if (!ctx->mixed && ctx->hslices > 1)
+        MISC(k_batch_sum(ctx->hslices - 1, Pp * Pp * Xb, ctx->Hb + Pp * Pp * Xb, 1.0, ctx->Hb, s));
       // I^X_ia = sum_YZ y_i^Z y_a^Y H^XYZ ; sigma^XW += sum_ia y_i^W y_a^W I^X_ia  (Alg. 6)
       // with H stored [Y][Z][x]: R1[Y][i][x] = sum_Z y_i^Z H[Y][Z][x], I6[i][a][x] = sum_Y y_a^Y R1[Y][i][x]
       RCHK(gemm(ctx, batched(mk(o, xb, P, Yo, P, false, ctx->Hb, Xb, false, ctx->R1, Xb), P, 0, Pp * Xb, o * Xb)));

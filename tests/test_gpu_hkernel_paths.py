@@ -1,6 +1,6 @@
 """The H-kernel (Alg. 6's three-way accumulation) at the edges of its tiles and of its copy pipeline: ranks one
 below, at and one above the 16-row blocks and 64-wide X tiles, chunks of fewer, as many and a few more
-grid points than stages, several X blocks -- Eq. 32 + 33 against the dense oracle in FP64 and in mixed precision."""
+grid points than stages, several X blocks, grid points in slices -- Eq. 32 + 33 against the dense oracle in FP64 and in mixed precision."""
 import numpy as np
 import pytest
 
@@ -24,7 +24,7 @@ def thc():
 
 # (nP, nQ, grid points per chunk, X block); 0: the planner's choice
 CASES = [(1, 3, 0, 0), (15, 17, 1, 0), (16, 21, 2, 0), (17, 20, 3, 0), (31, 25, 4, 0), (33, 23, 5, 0), (63, 30, 7, 0),
-         (64, 29, 8, 0), (65, 33, 9, 64), (80, 41, 11, 64), (129, 45, 0, 128)]
+         (64, 29, 8, 0), (65, 33, 9, 64), (80, 41, 11, 64), (129, 45, 0, 128), (16, 140, 0, 0), (33, 129, 50, 0)]
 
 
 @pytest.mark.parametrize("precision", [0, 1])
