@@ -64,6 +64,9 @@ hipError_t k_wsum(int64_t nb, int64_t len, const double* w, const double* X, int
                   double* out, hipStream_t s);
 hipError_t k_copy2d(int64_t batch, int64_t rows, int64_t cols, const double* src, int64_t lds, int64_t sbs,
                     double* dst, int64_t ldd, int64_t sbd, bool transpose, hipStream_t s);
+// dst = add + src (add laid out as dst; it may be dst)
+hipError_t k_copy2d_add(int64_t batch, int64_t rows, int64_t cols, const double* src, int64_t lds, int64_t sbs,
+                        const double* add, double* dst, int64_t ldd, int64_t sbd, bool transpose, hipStream_t s);
 hipError_t k_axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s);
 hipError_t k_hadamard(int64_t n, const double* x, const double* y, double alpha, double beta, double* out,
                       hipStream_t s);
@@ -92,6 +95,19 @@ hipError_t k_kr(int64_t o, int64_t v, int64_t P, const double* Yo, const double*
 hipError_t k_mp2_denom(int64_t rows0, int64_t rows, int64_t ov, int64_t v, const double* eps, int64_t o,
                        double* X, hipStream_t s);
 hipError_t k_fill(int64_t n, double val, double* x, hipStream_t s);
+// Arrays to clear together: end[k] = the elements of arrays 0 .. k.
+constexpr int CLEAR_MAX = 12;
+struct ClearSet {
+  int m = 0;
+  double* p[CLEAR_MAX];
+  int64_t end[CLEAR_MAX];
+  void add(double* x, int64_t n) {
+    p[m] = x;
+    end[m] = (m ? end[m - 1] : 0) + n;
+    ++m;
+  }
+};
+hipError_t k_clear(const ClearSet& c, hipStream_t s);
 hipError_t k_set_diag(int64_t n, const double* d, double* X, int64_t ld, hipStream_t s);
 
 // Set-up linear algebra on the device (eigen.hip).

@@ -163,15 +163,17 @@ __global__ void wsum_kernel(int64_t nb, int64_t len, const double* __restrict__ 
   }
 }
 
+// dst = src (transposed if asked), plus add (laid out as dst, which it may be) unless that is null
 __global__ void copy2d_kernel(int64_t batch, int64_t rows, int64_t cols, const double* __restrict__ src,
-                              int64_t lds, int64_t sbs, double* __restrict__ dst, int64_t ldd, int64_t sbd,
+                              int64_t lds, int64_t sbs, const double* add, double* dst, int64_t ldd, int64_t sbd,
                               int transpose) {
   const int64_t n = batch * rows * cols;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t b = e / (rows * cols), rc = e % (rows * cols);
     const int64_t r = rc / cols, c = rc % cols;
     const double x = transpose ? src[b * sbs + c * lds + r] : src[b * sbs + r * lds + c];
-    dst[b * sbd + r * ldd + c] = x;
+    const int64_t at = b * sbd + r * ldd + c;
+    dst[at] = add ? add[at] + x : x;
   }
 }
 
@@ -365,6 +367,22 @@ __global__ void fill_kernel(int64_t n, double val, double* __restrict__ x) {
     x[e] = val;
 }
 
+// Several arrays cleared by one launch: a residual starts with ten, each of a launch's length or less where the
+// system is small.
+__global__ void clear_kernel(const ClearSet c) {
+  const int64_t n = c.end[c.m - 1];
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+    double* p = c.p[0];
+    int64_t first = 0;
+    for (int k = 1; k < c.m; ++k)
+      if (e >= c.end[k - 1]) {
+        p = c.p[k];
+        first = c.end[k - 1];
+      }
+    p[e - first] = 0.0;
+  }
+}
+
 __global__ void set_diag_kernel(int64_t n, const double* __restrict__ d, double* __restrict__ X, int64_t ld) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
     X[e * ld + e] += d[e];
@@ -406,7 +424,11 @@ hipError_t k_wsum(int64_t nb, int64_t len, const double* w, const double* X, int
 }
 hipError_t k_copy2d(int64_t batch, int64_t rows, int64_t cols, const double* src, int64_t lds, int64_t sbs,
                     double* dst, int64_t ldd, int64_t sbd, bool transpose, hipStream_t s) {
-  LAUNCH(copy2d_kernel, dim3(nblocks(batch * rows * cols)), dim3(TPB), batch, rows, cols, src, lds, sbs, dst, ldd,
+  return k_copy2d_add(batch, rows, cols, src, lds, sbs, nullptr, dst, ldd, sbd, transpose, s);
+}
+hipError_t k_copy2d_add(int64_t batch, int64_t rows, int64_t cols, const double* src, int64_t lds, int64_t sbs,
+                        const double* add, double* dst, int64_t ldd, int64_t sbd, bool transpose, hipStream_t s) {
+  LAUNCH(copy2d_kernel, dim3(nblocks(batch * rows * cols)), dim3(TPB), batch, rows, cols, src, lds, sbs, add, dst, ldd,
          sbd, (int)transpose);
 }
 hipError_t k_axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s) {
@@ -479,6 +501,10 @@ hipError_t k_mp2_denom(int64_t r0, int64_t rows, int64_t ov, int64_t v, const do
 }
 hipError_t k_fill(int64_t n, double val, double* x, hipStream_t s) {
   LAUNCH(fill_kernel, dim3(nblocks(n)), dim3(TPB), n, val, x);
+}
+hipError_t k_clear(const ClearSet& c, hipStream_t s) {
+  if (c.m < 1 || c.m > CLEAR_MAX) return hipErrorInvalidValue;
+  LAUNCH(clear_kernel, dim3(nblocks(c.end[c.m - 1])), dim3(TPB), c);
 }
 hipError_t k_set_diag(int64_t n, const double* d, double* X, int64_t ld, hipStream_t s) {
   LAUNCH(set_diag_kernel, dim3(nblocks(n)), dim3(TPB), n, d, X, ld);

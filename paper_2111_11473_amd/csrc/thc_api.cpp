@@ -94,7 +94,7 @@ struct thc_ctx {
   double *xioo = nullptr, *xivv = nullptr, *s38 = nullptr, *dvecA = nullptr, *trK = nullptr;
   double *ej = nullptr, *ek = nullptr;
   double *Fin = nullptr, *Fh = nullptr;  // n x n, blocks [oo | ov | vo | vv]
-  double *Jov = nullptr, *Jvo = nullptr;
+  double* Jov = nullptr;
   // assembly
   double *ST = nullptr, *Dt = nullptr, *K29 = nullptr, *Qm = nullptr, *ot = nullptr, *vt = nullptr, *E9 = nullptr;
   double *tmpoP = nullptr, *tmpvP = nullptr, *Fxoo = nullptr, *Fxvv = nullptr, *Tf = nullptr, *fd = nullptr;
@@ -573,7 +573,7 @@ std::vector<BufSpec> persistent_list(thc_ctx* ctx) {
       {&ctx->At, (size_t)(P * nL)}, {&ctx->Hh, (size_t)(P * nL)}, {&ctx->xioo, (size_t)(o * o)},
       {&ctx->xivv, (size_t)(v * v)}, {&ctx->s38, (size_t)ov}, {&ctx->dvecA, (size_t)nL}, {&ctx->trK, (size_t)nL},
       {&ctx->ej, (size_t)nL}, {&ctx->ek, (size_t)(nL * 64)}, {&ctx->Fin, (size_t)(n * n)}, {&ctx->Fh, (size_t)(n * n)},
-      {&ctx->Jov, (size_t)ov}, {&ctx->Jvo, (size_t)ov},
+      {&ctx->Jov, (size_t)ov},
       // assembly
       {&ctx->ST, (size_t)PP}, {&ctx->Dt, (size_t)(P * nL)}, {&ctx->K29, (size_t)(P * nL)}, {&ctx->Qm, (size_t)PP},
       {&ctx->ot, (size_t)PP}, {&ctx->vt, (size_t)PP}, {&ctx->E9, (size_t)PP}, {&ctx->tmpoP, (size_t)(o * P)},
@@ -1071,16 +1071,20 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
   const bool singles = sres && t1 != nullptr;  // T1 dressing needed (t1 given)
   const double *Yo = ctx->Yo, *Yv = ctx->Yv, *xo = ctx->xo, *xv = ctx->xv;
 
-  RCHK(zero(ctx, ctx->sig, PP));
-  RCHK(zero(ctx, ctx->sig1, ov));
-  RCHK(zero(ctx, ctx->sig28, ctx->KS * PP));
-  RCHK(zero(ctx, ctx->C3, PP));
-  RCHK(zero(ctx, ctx->xioo, o * o));
-  RCHK(zero(ctx, ctx->xivv, v * v));
-  RCHK(zero(ctx, ctx->s38, ov));
-  RCHK(zero(ctx, ctx->Fin, n * n));
-  RCHK(zero(ctx, ctx->dvecA, nL));
-  RCHK(zero(ctx, ctx->trK, nL));
+  {
+    ClearSet c;
+    c.add(ctx->sig, PP);
+    c.add(ctx->sig1, ov);
+    c.add(ctx->sig28, ctx->KS * PP);
+    c.add(ctx->C3, PP);
+    c.add(ctx->xioo, o * o);
+    c.add(ctx->xivv, v * v);
+    c.add(ctx->s38, ov);
+    c.add(ctx->Fin, n * n);
+    c.add(ctx->dvecA, nL);
+    c.add(ctx->trK, nL);
+    MISC(k_clear(c, s));
+  }
 
   // ---------------- fused pass over blocks of Cholesky vectors (Alg. 1, 2, 3, 8) -------------
   ctx->section = "gemm@fused";
@@ -1099,8 +1103,7 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
       // tmpoo[A] = Lov t1^T (o x o), also in the [i][A][k] layout for the Fock K-term
       RCHK(gemm(ctx, k64(batched(mk(o, o, v, Lov, v, false, t1, v, true, ctx->tmpoo, o), nb, ov, 0, o * o))));
       RCHK(gemm(ctx, k64(batched(mk(o, o, v, Lov, v, false, t1, v, true, ctx->tmpooT, nb * o), nb, ov, 0, o))));
-      MISC(k_copy2d(1, nb * o, o, Loo, o, 0, ctx->Lhoo, o, 0, false, s));
-      MISC(k_axpby(nb * o * o, 1.0, ctx->tmpoo, 1.0, ctx->Lhoo, s));
+      MISC(k_copy2d_add(1, nb * o, o, Loo, o, 0, ctx->tmpoo, ctx->Lhoo, o, 0, false, s));
       Lhoo = ctx->Lhoo;
       MISC(k_trace_sq(nb, o, ctx->tmpoo, ctx->trK + A0, s));
       // d_A = sum_ia t_ia L_ia^A
@@ -1109,8 +1112,7 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
       RCHK(gemm(ctx, k64(batched(mk(v, o, v, Lvv, v, false, t1, v, true, ctx->Pv, o), nb, v * v, 0, v * o))));
       RCHK(gemm(ctx, k64(batched(mk(v, o, v, Lvv, v, false, t1, v, true, ctx->PvT, nb * o), nb, v * v, 0, o))));
       // Lhvo[A] = Lov^T + Lvv t1^T - t1^T Lhoo
-      MISC(k_copy2d(nb, v, o, Lov, v, ov, ctx->Lhvo, o, v * o, true, s));
-      MISC(k_axpby(nb * v * o, 1.0, ctx->Pv, 1.0, ctx->Lhvo, s));
+      MISC(k_copy2d_add(nb, v, o, Lov, v, ov, ctx->Pv, ctx->Lhvo, o, v * o, true, s));
       RCHK(gemm(ctx, k64(batched(mk(v, o, o, t1, v, true, ctx->Lhoo, o, false, ctx->Lhvo, o, -1.0, 1.0), nb, 0, o * o, v * o))));
       // Fock: inner += 2 sum_A d_A L^A - sum_A (L^A[:, vir] t1^T) L^A[occ, :]
       MISC(k_wsum(nb, o * o, ctx->dvecA + A0, Loo, o * o, 2.0, ctx->Fin, s));  // oo block written densely below
@@ -1206,8 +1208,7 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
       // J part of the vo block: (2 sum_A d_A L_ov^A)^T (L symmetric)
       RCHK(zero(ctx, ctx->Jov, ov));
       MISC(k_wsum(nL, ov, ctx->dvecA, ctx->Lov, ov, 2.0, ctx->Jov, s));
-      MISC(k_copy2d(1, v, o, ctx->Jov, v, 0, ctx->Jvo, o, 0, true, s));
-      MISC(k_axpby(v * o, 1.0, ctx->Jvo, 1.0, Ivo, s));
+      MISC(k_copy2d_add(1, v, o, ctx->Jov, v, 0, Ivo, Ivo, o, 0, true, s));
       // F^ = (1 - tau) inner (1 + tau)
       MISC(k_copy2d(1, o, v, Iov, v, 0, Fov, v, 0, false, s));
       MISC(k_copy2d(1, o, o, Ioo, o, 0, Foo, o, 0, false, s));
@@ -1244,10 +1245,8 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
   }
   if (mask & THC_TERM_EQ41) {
     // Alg. 9: E = Go o vt - Gv o ot, vt = Yv^T (F^vv + xi_vv) Yv, ot = Yo^T (F^oo + xi_oo)^T Yo
-    MISC(k_copy2d(1, o, o, Foo, o, 0, ctx->Fxoo, o, 0, false, s));
-    MISC(k_axpby(o * o, 1.0, ctx->xioo, 1.0, ctx->Fxoo, s));
-    MISC(k_copy2d(1, v, v, Fvv, v, 0, ctx->Fxvv, v, 0, false, s));
-    MISC(k_axpby(v * v, 1.0, ctx->xivv, 1.0, ctx->Fxvv, s));
+    MISC(k_copy2d_add(1, o, o, Foo, o, 0, ctx->xioo, ctx->Fxoo, o, 0, false, s));
+    MISC(k_copy2d_add(1, v, v, Fvv, v, 0, ctx->xivv, ctx->Fxvv, v, 0, false, s));
     RCHK(gemm(ctx, mk(o, P, o, ctx->Fxoo, o, true, Yo, P, false, ctx->tmpoP, P)));
     RCHK(gemm(ctx, mk(P, P, o, Yo, P, true, ctx->tmpoP, P, false, ctx->ot, P)));
     RCHK(gemm(ctx, mk(v, P, v, ctx->Fxvv, v, false, Yv, P, false, ctx->tmpvP, P)));
@@ -1401,8 +1400,7 @@ int residual_impl(thc_ctx* ctx, const double* T, const double* t1, uint32_t mask
   if (singles) {  // with t1 = 0 the Fock matrix is diag(eps) and these terms vanish
     if (mask & THC_TERM_EQ42) {
       // F^_ai + 2 Yo diag(T f) Yv^T - Yo (T o Mf^T) Yv^T, Mf = Yo^T F^ov Yv, f = diag(Mf)
-      MISC(k_copy2d(1, o, v, Fvo, o, 0, ctx->tmpov, v, 0, true, s));
-      MISC(k_axpby(ov, 1.0, ctx->tmpov, 1.0, ctx->sig1, s));
+      MISC(k_copy2d_add(1, o, v, Fvo, o, 0, ctx->sig1, ctx->sig1, v, 0, true, s));
       RCHK(gemm(ctx, mk(o, P, v, Fov, v, false, Yv, P, false, ctx->tmpoP, P)));
       RCHK(gemm(ctx, mk(P, P, o, ctx->tmpoP, P, true, Yo, P, false, ctx->Qm, P)));  // Mf^T
       MISC(k_diag(P, ctx->Qm, P, ctx->fd, s));
