@@ -57,6 +57,7 @@ struct thc_ctx {
   bool lvv_resident = true;   // the vv Cholesky block is held; else regenerated per fused-pass block
   int64_t nb = 0, KS = 1, Xb = 0, Ic = 0, Xc = 0, X7 = 0;
   int hslices = 1;  // slices of the grid points in the FP64 H-kernel, each with its own H
+  int64_t nb0 = 0;  // vectors per block that the plan leaves room for beside the Alg. 6 region (nb spreads over it)
 
   std::vector<void*> allocs;
   size_t arena_bytes = 0;  // length of the library-allocated arena (0: the caller's workspace)
@@ -531,6 +532,7 @@ int check_finite_host(thc_ctx* ctx, const double* x, size_t n, const char* what)
 // 16 P Pp^2 Q / Ic bytes, independent of Xb), then the largest Xb (each H block recomputes the
 // G chunks, the paper's redundancy).
 constexpr double MEM_CAP = 270.0e9;   // at most this much device memory without a workspace
+constexpr double ARENA_KEEP = 9.6e9;  // the longest arena kept for the next context (see ArenaBlock)
 constexpr size_t ALIGN_D = 32;       // buffers start on 256-byte boundaries
 
 struct BufSpec {
@@ -561,14 +563,7 @@ std::vector<BufSpec> persistent_list(thc_ctx* ctx) {
       {&ctx->dvec, (size_t)(std::max<int64_t>(dm, 1) * (PP + ov))}, {&ctx->derr, (size_t)(std::max<int64_t>(dm, 1) * (PP + ov))},
       {&ctx->dT, (size_t)(PP + ov)},
       {&ctx->sig, (size_t)PP}, {&ctx->sig1, (size_t)ov}, {&ctx->sigh, (size_t)PP}, {&ctx->scal, 64},
-      // fused pass
-      {&ctx->Lhoo, (size_t)(nb * o * o)}, {&ctx->Lhvo, (size_t)(nb * v * o)}, {&ctx->tmpoo, (size_t)(nb * o * o)},
-      {&ctx->tmpooT, (size_t)(nb * o * o)}, {&ctx->Pv, (size_t)(nb * v * o)}, {&ctx->PvT, (size_t)(nb * v * o)},
-      {&ctx->LovYv, (size_t)(nb * o * P)}, {&ctx->Wv, (size_t)(nb * v * P)}, {&ctx->Bvv, (size_t)(nb * PP)},
-      {&ctx->Woo, (size_t)(nb * o * P)}, {&ctx->Boo, (size_t)(nb * PP)}, {&ctx->Ccat, (size_t)(nb * PP)},
-      {&ctx->Dcat, (size_t)(nb * PP)}, {&ctx->Wvo, (size_t)(nb * o * P)}, {&ctx->Y1, (size_t)(nb * o * P)},
-      {&ctx->Gm, (size_t)(nb * ov)}, {&ctx->GY, (size_t)(nb * o * P)}, {&ctx->TA, (size_t)(P * nb)},
-      {&ctx->tmpov, (size_t)(nb * std::max(std::max(ov, v * v), o * o))},
+      // fused pass: sums over the blocks
       {&ctx->sig28, (size_t)(ctx->KS * PP)}, {&ctx->C3, (size_t)PP}, {&ctx->Abar, (size_t)(P * nL)},
       {&ctx->At, (size_t)(P * nL)}, {&ctx->Hh, (size_t)(P * nL)}, {&ctx->xioo, (size_t)(o * o)},
       {&ctx->xivv, (size_t)(v * v)}, {&ctx->s38, (size_t)ov}, {&ctx->dvecA, (size_t)nL}, {&ctx->trK, (size_t)nL},
@@ -583,6 +578,19 @@ std::vector<BufSpec> persistent_list(thc_ctx* ctx) {
       {&ctx->S7, (size_t)(P * ov)}, {&ctx->R7, (size_t)(P * ov)}, {&ctx->Cx, (size_t)(P * Q)}, {&ctx->Dx, (size_t)(P * Q)},
       {&ctx->gws, (size_t)GEMM_WS},
   };
+}
+
+// Buffers of one block of nb vectors of the fused pass (Ccat and Dcat also of the MP2 density): nothing in
+// them outlives the pass.
+std::vector<BufSpec> fused_list(thc_ctx* ctx, int64_t nb) {
+  const int64_t o = ctx->o, v = ctx->v, P = ctx->P, PP = P * P, ov = ctx->ov;
+  return {{&ctx->Lhoo, (size_t)(nb * o * o)}, {&ctx->Lhvo, (size_t)(nb * v * o)}, {&ctx->tmpoo, (size_t)(nb * o * o)},
+          {&ctx->tmpooT, (size_t)(nb * o * o)}, {&ctx->Pv, (size_t)(nb * v * o)}, {&ctx->PvT, (size_t)(nb * v * o)},
+          {&ctx->LovYv, (size_t)(nb * o * P)}, {&ctx->Wv, (size_t)(nb * v * P)}, {&ctx->Bvv, (size_t)(nb * PP)},
+          {&ctx->Woo, (size_t)(nb * o * P)}, {&ctx->Boo, (size_t)(nb * PP)}, {&ctx->Ccat, (size_t)(nb * PP)},
+          {&ctx->Dcat, (size_t)(nb * PP)}, {&ctx->Wvo, (size_t)(nb * o * P)}, {&ctx->Y1, (size_t)(nb * o * P)},
+          {&ctx->Gm, (size_t)(nb * ov)}, {&ctx->GY, (size_t)(nb * o * P)}, {&ctx->TA, (size_t)(P * nb)},
+          {&ctx->tmpov, (size_t)(nb * std::max(std::max(ov, v * v), o * o))}};
 }
 
 // Alg. 6 region for an H block of Xb ranks and grid-point chunks of Ic points.  The mixed path's
@@ -673,7 +681,19 @@ double plan_bytes(thc_ctx* ctx, int64_t slots) {
   const double r6 = list_bytes(ctx->quintic ? quintic_list(ctx) : region6_list(ctx));
   return list_bytes(persistent_list(ctx)) +
          8.0 * (double)tile_table_doubles(ctx->Pp, ctx->Xb, slots) * (ctx->opt.precision >= 1 ? 2.0 : 1.0) +
-         std::max(r6, 8.0 * (double)setup_doubles(ctx)) + list_bytes(alg7_list(ctx));
+         std::max(std::max(r6, 8.0 * (double)setup_doubles(ctx)) + list_bytes(fused_list(ctx, ctx->nb0)),
+                  list_bytes(fused_list(ctx, ctx->nb))) +
+         list_bytes(alg7_list(ctx));
+}
+
+// Tile edge of the first block's sum_A C^A T C^A^T, as residual_impl issues it.
+int alg1_tile_edge(const thc_ctx* ctx) {
+  Gemm g;
+  g.M = g.N = ctx->P;
+  g.K = ctx->nb * ctx->P;
+  g.ksplit = (int)ctx->KS;
+  g.upper = true;
+  return gemm_tile_edge_split(g);
 }
 
 // Picks the blocking (KS, Xb, Ic, X7, the residency of the vv block) for fused-pass blocks of nb vectors and
@@ -683,20 +703,13 @@ int plan_with_block(thc_ctx* ctx, double budget, int64_t slots, int64_t nb) {
   const int64_t Pp = ctx->Pp = ((P + 15) / 16) * 16;  // Y, Z ranks of H padded to its 16-wide blocks
   const int64_t P64 = ((P + 63) / 64) * 64;           // X ranks padded to its 64-lane tiles
   const thc_options& op = ctx->opt;
-  ctx->nb = nb;
+  ctx->nb = ctx->nb0 = nb;
   ctx->hslices = 1;
   // split of the N_L P-deep sum of Alg. 1: at most 512 workgroups of 128 x 128 tiles (one round
   // at two per CU), counting the tiles on and above the diagonal (the product is symmetric)
   const int64_t nt128 = (P + 127) / 128, t128 = nt128 * (nt128 + 1) / 2;
   ctx->KS = std::max<int64_t>(1, std::min<int64_t>(16, 512 / t128));
-  {
-    Gemm g;  // the first block's sum_A C^A T C^A^T, as residual_impl issues it
-    g.M = g.N = P;
-    g.K = nb * P;
-    g.ksplit = (int)ctx->KS;
-    g.upper = true;
-    ctx->alg1_tile = gemm_tile_edge_split(g);
-  }
+  ctx->alg1_tile = alg1_tile_edge(ctx);
   // the vv Cholesky block: held (caller inputs always); synthetic inputs regenerate it block by
   // block in the fused pass when asked or when it would take more than 40% of the budget
   ctx->lvv_resident = !ctx->synth || (!(op.flags & THC_FLAG_STREAM_LVV) && 8.0 * (double)nL * v * v < 0.4 * budget);
@@ -709,7 +722,7 @@ int plan_with_block(thc_ctx* ctx, double budget, int64_t slots, int64_t nb) {
   const double per7 = 8.0 * (double)(o * P + 4 * o * Q + 2 * ov);
   if (X7 <= 0) X7 = std::max<int64_t>(1, (int64_t)(std::min(24.0e9, 0.1 * budget) / per7));
   ctx->X7 = std::min(X7, P);
-  const double pers = list_bytes(persistent_list(ctx));
+  const double pers = list_bytes(persistent_list(ctx)) + list_bytes(fused_list(ctx, nb));
   const double a7 = list_bytes(alg7_list(ctx));
   const double setup = 8.0 * (double)setup_doubles(ctx);
   // Eq. 32 + 33 by Alg. 4 and 5 (asked for, or estimated faster) instead of Alg. 6
@@ -785,8 +798,15 @@ int plan_with_block(thc_ctx* ctx, double budget, int64_t slots, int64_t nb) {
 // panels stay no larger than they are at P = 1000 with 64 (64e6 values), as many as that allows in blocks of
 // equal length: the pass is some 75 launches a block, so small ranks want few blocks and middling ones
 // products over many vectors.  Residual at P = 50, nL = 70: 1.05 ms in blocks of 64, 0.85 in one; P = 620,
-// nL = 930: 111.2 ms in blocks of 64, 104.0 of 155; a solve at P = 120:
-// 14.0 -> 10.1 ms.  Mixed precision keeps 64, which its FP32 sums over vectors and their splits follow.  The longer block is taken only where the budget leaves the rest of the plan as it is.
+// nL = 930: 111.2 ms in blocks of 64, 104.0 of 155; a solve at P = 120: 14.0 -> 10.1 ms.  Mixed precision
+// keeps 64, which its FP32 sums over vectors and their splits follow.
+// A longer block leaves the rest of the plan as it is: its buffers spread from the place of the shorter
+// block's over the end of the Alg. 6 region before it, which the residual fills only after the pass (the
+// region's zero padding is then not kept: nothing but padding is computed from it).  Memory costs a
+// context the driver's clearing, 28 ms a GB (see ArenaBlock), so the plan grows by it only up to the
+// length of an arena that is kept for the next context; past that the blocks are cut until they fit the
+// memory of 64 vectors.  With memory of their own they cost 29% of a set-up at o = 22 (221 -> 286 ms, one
+// after another), 16% at o = 24, 6% at o = 30.
 int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
   const int64_t nL = ctx->nL, P = ctx->P, n2 = std::max(std::max(P, ctx->o), ctx->v);
   int64_t nb = ctx->opt.a_block > 0 ? ctx->opt.a_block : std::max<int64_t>(1, std::min<int64_t>(64, (int64_t)(4.0e9 / (32.0 * P * P))));
@@ -794,17 +814,14 @@ int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
   const int rc = plan_with_block(ctx, budget, slots, nb);
   const int64_t most = std::min<int64_t>(1024, (int64_t)(64.0e6 / ((double)n2 * n2)));
   if (rc != THC_OK || ctx->opt.a_block > 0 || ctx->opt.precision >= 1 || most <= nb || nb == nL) return rc;
-  const int64_t blocks = (nL + most - 1) / most;
-  const int64_t longer = (nL + blocks - 1) / blocks;
-  const int64_t Xb = ctx->Xb, Ic = ctx->Ic, X7 = ctx->X7, nq = ctx->nq, jq = ctx->jq;
-  const bool resident = ctx->lvv_resident;
-  const int hslices = ctx->hslices;
-  if (longer <= nb) return rc;
-  if (plan_with_block(ctx, budget, slots, longer) == THC_OK && ctx->Xb == Xb && ctx->Ic == Ic && ctx->X7 == X7 &&
-      ctx->nq == nq && ctx->jq == jq && ctx->lvv_resident == resident && ctx->hslices == hslices && plan_bytes(ctx, slots) <= budget)
-    return THC_OK;
-  ctx->err.clear();
-  return plan_with_block(ctx, budget, slots, nb);
+  const double limit = std::min(budget, std::max(plan_bytes(ctx, slots), ARENA_KEEP));
+  for (int64_t blocks = (nL + most - 1) / most;; ++blocks) {
+    const int64_t longer = (nL + blocks - 1) / blocks;
+    ctx->nb = std::max(longer, nb);
+    if (longer <= nb || plan_bytes(ctx, slots) <= limit) break;
+  }
+  ctx->alg1_tile = alg1_tile_edge(ctx);
+  return THC_OK;
 }
 
 // The plan for the context's budget (its workspace, else the device's free memory up to
@@ -812,11 +829,11 @@ int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
 // The arena of the context destroyed last, kept for the next one.  A freed block is cleared by the
 // driver before it can be allocated again, at about 38 GB/s, so that programs that set up one system
 // after another wait for it in hipMalloc once all memory has been handed out: 161 ms for the 6.2 GB of
-// o = 20, where the whole set-up takes 13 ms.  At most one block is held, of at most 1/32 of the
-// device's memory and only while half of that memory is free; a context that cannot use it (another
-// device, longer, or shorter than half of it) returns it to the driver before it allocates.  Blocks
-// come in with their work finished and belong to nobody while they are here, so any thread or
-// stream may take one.
+// o = 20, where the whole set-up takes 13 ms.  At most one block is held, of at most ARENA_KEEP
+// bytes and 1/16 of the device's memory, and only while half of that memory is free; a context that
+// cannot use it (another device, longer, or shorter than half of it) returns it to the driver before it
+// allocates.  Blocks come in with their work finished and belong to nobody while they are here, so any
+// thread or stream may take one.
 struct ArenaBlock {
   void* p = nullptr;
   size_t bytes = 0;
@@ -849,7 +866,7 @@ void arena_keep(ArenaBlock& b) {  // b: afterwards what was kept before, or b it
   size_t freeb = 0, totalb = 0;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != b.device || hipMemGetInfo(&freeb, &totalb) != hipSuccess) return;
-  if (b.bytes > totalb / 32 || freeb < totalb / 2) return;
+  if ((double)b.bytes > ARENA_KEEP || b.bytes > totalb / 16 || freeb < totalb / 2) return;
   std::lock_guard<std::mutex> lock(arena_mutex);
   b.swap(arena_kept());
 }
@@ -895,12 +912,17 @@ int plan_and_alloc(thc_ctx* ctx) {
   std::vector<BufSpec> pers = persistent_list(ctx);
   pers.push_back({&tb, (tiles.size() + tiles32.size() + 1) / 2});
   const std::vector<BufSpec> r6 = ctx->quintic ? quintic_list(ctx) : region6_list(ctx), a7 = alg7_list(ctx);
-  size_t np = 0, n6 = 0, n7 = 0;
+  const std::vector<BufSpec> fused = fused_list(ctx, ctx->nb);
+  size_t np = 0, n6 = 0, n7 = 0, nf = 0, nf0 = 0;
   for (const auto& a : pers) np += aligned(a.n);
   for (const auto& a : r6) n6 += aligned(a.n);
   for (const auto& a : a7) n7 += aligned(a.n);
+  for (const auto& a : fused) nf += aligned(a.n);
+  for (const auto& a : fused_list(ctx, ctx->nb0)) nf0 += aligned(a.n);
   const size_t nsetup = setup_doubles(ctx);
-  const size_t total = np + std::max(n6, nsetup) + n7;
+  // the Alg. 6 region and, at its end, the fused pass's block buffers (over the region's end if nb > nb0)
+  const size_t nregion = std::max(std::max(n6, nsetup) + nf0, nf);
+  const size_t total = np + nregion + n7;
   if (ctx->ws) {
     if (8.0 * (double)total > (double)ctx->ws_bytes) { ctx->err = "workspace too small for the plan"; return THC_ENOMEM; }
     ctx->arena = (double*)ctx->ws;
@@ -931,7 +953,8 @@ int plan_and_alloc(thc_ctx* ctx) {
   ctx->setup_scratch = at;  // the set-up's scratch overlays the Alg. 6 region
   ctx->setup_len = std::max(n6, nsetup);
   for (const auto& a : r6) { *a.p = at; at += aligned(a.n); }
-  at = ctx->setup_scratch + std::max(n6, nsetup);
+  at = ctx->setup_scratch + nregion - nf;
+  for (const auto& a : fused) { *a.p = at; at += aligned(a.n); }
   for (const auto& a : a7) { *a.p = at; at += aligned(a.n); }
   ctx->Ec32 = ctx->opt.precision >= 1 && !ctx->quintic ? reinterpret_cast<float*>(ctx->Ec) : nullptr;
   ctx->Fc32 = ctx->opt.precision >= 1 && !ctx->quintic ? reinterpret_cast<float*>(ctx->Fc) : nullptr;
@@ -951,10 +974,10 @@ int plan_and_alloc(thc_ctx* ctx) {
   return THC_OK;
 }
 
-// The Alg. 6 operands whose padding must stay zero, cleared once the set-up no longer uses the
-// region as scratch.
+// The padding of the Alg. 6 operands, cleared once the set-up no longer uses the region as scratch.  (Nothing but
+// padding is computed from it, so the long blocks of the fused pass may overwrite it later.)
 int clear_region6(thc_ctx* ctx) {
-  if (ctx->quintic) return THC_OK;  // Alg. 4 and 5 need no zero padding
+  if (ctx->quintic) return THC_OK;  // Alg. 4 and 5 have no padding
   const int64_t o = ctx->o, v = ctx->v, Pp = ctx->Pp, Xb = ctx->Xb, Ic = ctx->Ic;
   RCHK(zero(ctx, ctx->C6, o * Xb * Pp));
   RCHK(zero(ctx, ctx->D6, v * Xb * Pp));
