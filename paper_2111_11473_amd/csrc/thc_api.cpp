@@ -676,11 +676,16 @@ std::vector<BufSpec> quintic_list(thc_ctx* ctx) {
           {&ctx->qI1, (size_t)(n * w * P)}};
 }
 
+// Doubles the plan keeps for the H-kernels' tile tables (the FP32 kernel's has half as many tiles).
+size_t table_doubles(const thc_ctx* ctx, int64_t slots) {
+  return tile_table_doubles(ctx->Pp, ctx->Xb, slots) * (ctx->opt.precision >= 1 ? 2 : 1);
+}
+
 // Device bytes of the plan in ctx.
 double plan_bytes(thc_ctx* ctx, int64_t slots) {
   const double r6 = list_bytes(ctx->quintic ? quintic_list(ctx) : region6_list(ctx));
   return list_bytes(persistent_list(ctx)) +
-         8.0 * (double)tile_table_doubles(ctx->Pp, ctx->Xb, slots) * (ctx->opt.precision >= 1 ? 2.0 : 1.0) +
+         8.0 * (double)table_doubles(ctx, slots) +
          std::max(std::max(r6, 8.0 * (double)setup_doubles(ctx)) + list_bytes(fused_list(ctx, ctx->nb0)),
                   list_bytes(fused_list(ctx, ctx->nb))) +
          list_bytes(alg7_list(ctx));
@@ -899,6 +904,7 @@ int plan_and_alloc(thc_ctx* ctx) {
     budget = std::min(MEM_CAP, (double)freeb + (double)kept.bytes - 2.0e9);
   }
   RCHK(choose_plan(ctx, budget, ctx->hslots));
+  const size_t ntable = table_doubles(ctx, ctx->hslots);
   ctx->hslots = h_run_length(ctx->Pp, ctx->Xb, ctx->hslots);
   const std::vector<uint32_t> tiles = h_tiles(ctx->Pp, ctx->Xb, ctx->hslots);
   std::vector<uint32_t> tiles32;
@@ -910,7 +916,9 @@ int plan_and_alloc(thc_ctx* ctx) {
   }
   double* tb = nullptr;
   std::vector<BufSpec> pers = persistent_list(ctx);
-  pers.push_back({&tb, (tiles.size() + tiles32.size() + 1) / 2});
+  // the planned length, which runs shorter than the device's slots do not fill: a workspace of the bytes that
+  // a context reports then gives the same plan
+  pers.push_back({&tb, std::max((tiles.size() + tiles32.size() + 1) / 2, ntable)});
   const std::vector<BufSpec> r6 = ctx->quintic ? quintic_list(ctx) : region6_list(ctx), a7 = alg7_list(ctx);
   const std::vector<BufSpec> fused = fused_list(ctx, ctx->nb);
   size_t np = 0, n6 = 0, n7 = 0, nf = 0, nf0 = 0;
