@@ -334,7 +334,17 @@ int thc_dgemm(int transA, int transB, int64_t M, int64_t N, int64_t K, double al
               int64_t ldc, int64_t sC, int64_t batch, void* stream);
 
 const char* thc_last_error(const thc_ctx* ctx);
+/* Waits for the context's stream and releases what the context holds.  Working memory that the library
+ * allocated itself stays with the library for the next context if it is at most 9.6 GB and a sixteenth
+ * of the device's memory and at least half of that memory is free: the driver clears freed memory (28 ms
+ * a GB) before it hands it out again.  At most one block is kept in a process.  The next context uses
+ * it or returns it to the driver, an allocation of the library that finds too little memory returns
+ * it, and so does thc_release_cached_memory.  A caller's workspace is never kept. */
 void thc_destroy(thc_ctx* ctx);
+/* Returns the memory that thc_destroy kept (if any) to the driver, for other users of the device: call
+ * it after the last context, or before another allocator needs the memory.  May be called from any
+ * thread at any time, contexts in use are not affected.  THC_OK, or THC_EDEVICE if freeing failed. */
+int thc_release_cached_memory(void);
 
 /* ---- Learned starting guess -------------------------------------------------------------------
  * Not part of the paper: a small network proposes, per rank index P of the pseudo-canonical

@@ -837,7 +837,7 @@ int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
 // o = 20, where the whole set-up takes 13 ms.  At most one block is held, of at most ARENA_KEEP
 // bytes and 1/16 of the device's memory, and only while half of that memory is free; a context that
 // cannot use it (another device, longer, or shorter than half of it) returns it to the driver before it
-// allocates.  Blocks come in with their work finished and belong to nobody while they are here, so any
+// allocates, and thc_release_cached_memory returns it at any time.  Blocks come in with their work finished and belong to nobody while they are here, so any
 // thread or stream may take one.
 struct ArenaBlock {
   void* p = nullptr;
@@ -2980,6 +2980,15 @@ void thc_mlp_destroy(thc_mlp* ctx) {
 }
 
 const char* thc_last_error(const thc_ctx* ctx) { return ctx ? ctx->err.c_str() : "null context"; }
+
+int thc_release_cached_memory(void) {
+  ArenaBlock b;
+  arena_take(b);
+  if (!b.p) return THC_OK;
+  const hipError_t e = hipFree(b.p);
+  b.p = nullptr;
+  return e == hipSuccess ? THC_OK : THC_EDEVICE;
+}
 
 void thc_destroy(thc_ctx* ctx) {
   if (!ctx) return;

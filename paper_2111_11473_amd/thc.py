@@ -36,7 +36,7 @@ SYMBOLS = ["thc_create", "thc_build_factors", "thc_residual", "thc_residual_term
            "thc_energy",
            "thc_get_state", "thc_set_state", "thc_memory_bytes", "thc_plan",
            "thc_set_synthetic", "thc_synth_gamma", "thc_mp2_density", "thc_create_with_workspace", "thc_plan_query", "thc_synth_normals", "thc_synth_cholesky", "thc_synth_energies", "thc_cp_als", "thc_profile", "thc_profile_get", "thc_profile_flops", "thc_dgemm",
-           "thc_last_error", "thc_destroy",
+           "thc_last_error", "thc_destroy", "thc_release_cached_memory",
            "thc_guess_features", "thc_guess_apply", "thc_set_guess_network", "thc_set_shift", "thc_working", "thc_guess_targets",
            "thc_mlp_create", "thc_mlp_set_norm", "thc_mlp_fit_norm", "thc_mlp_get_norm", "thc_mlp_num_params", "thc_mlp_get_params", "thc_mlp_set_params",
            "thc_mlp_forward", "thc_mlp_forward_noalloc", "thc_mlp_loss_grad", "thc_mlp_train_step", "thc_mlp_infer", "thc_mlp_last_error",
@@ -125,6 +125,7 @@ def load(path: str = LIB_PATH):
     lib.thc_last_error.restype = C.c_char_p
     lib.thc_destroy.argtypes = [VP]
     lib.thc_destroy.restype = None
+    lib.thc_release_cached_memory.argtypes = []
     lib.thc_guess_features.argtypes = [VP, P]
     lib.thc_guess_apply.argtypes = [VP, P, I64]
     lib.thc_set_guess_network.argtypes = [VP, VP]
@@ -274,6 +275,14 @@ def cp_als(A, X, Y, Z, sweeps, w1=None, w2=None, w3=None, cg_tol=1e-12, cg_maxit
     if rc != 0:
         raise ThcError(rc, "thc_cp_als failed")
     return (list(obj) if objective else None), its.value
+
+
+def release_cached_memory():
+    """Returns to the driver the working memory that the library keeps from the context closed last (up to 9.6 GB)
+    for the next one: after the last context, or before torch needs all of the device's memory."""
+    rc = load().thc_release_cached_memory()
+    if rc != 0:
+        raise ThcError(rc, "thc_release_cached_memory failed")
 
 
 class THC:

@@ -1,0 +1,132 @@
+"""The working memory kept from a closed context: reused by the next one, reported by it, returned to the driver by
+thc_release_cached_memory, and without influence on any result."""
+import gc
+import threading
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def thc():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2111_11473_amd import thc as mod
+    mod.load()
+    return mod
+
+
+def _free():
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+def _inputs(o, v, nL, P, Q, seed=3):
+    import torch
+    rng = np.random.default_rng(seed)
+    n = o + v
+    L = rng.standard_normal((nL, n, n)) * (0.1 / n)
+    L = L + L.transpose(0, 2, 1)
+    eps = np.concatenate([-np.sort(rng.uniform(0.5, 3.0, o))[::-1], np.sort(rng.uniform(0.3, 4.0, v))])
+    x = [rng.standard_normal((k, r)) for r in (P, Q) for k in (o, v)]
+    t = lambda a: torch.tensor(a, dtype=torch.float64, device="cuda").contiguous()
+    return [t(a) for a in (L, eps, *x)]
+
+
+N = (8, 40, 60, 140, 200)  # P^2 + o v > 16384: the iteration's inner products run over many blocks
+
+
+def _solve(thc, n, args, workspace=None, **kw):
+    """Everything one context computes, and the free memory before and after it is closed."""
+    import torch
+    ctx = thc.THC(*n, workspace=workspace, **kw)
+    Z = ctx.build_factors(*args)
+    t1 = torch.linspace(-0.01, 0.01, n[0] * n[1], dtype=torch.float64, device="cuda").reshape(n[0], n[1])
+    out = [Z, *ctx.residual(Z, t1), *ctx.mp2_density(Z)]
+    its = ctx.iterate(tol=1e-9, maxit=30, raise_on_notconv=False)
+    e = ctx.energy()
+    out = [x.clone() for x in (*out, *ctx.get_state())] + [torch.tensor([float(its[0]), its[1], e], dtype=torch.float64)]
+    inside = _free()
+    need = ctx.plan()["device_bytes"]
+    ctx.close()
+    return out, need, inside, _free()
+
+
+def test_kept_memory_is_returned_on_request(thc):
+    gc.collect()
+    args = _inputs(*N)
+    thc.release_cached_memory()
+    _, need, inside, after = _solve(thc, N, args)
+    assert after - inside < need / 2  # kept
+    thc.release_cached_memory()
+    assert _free() - after >= need
+    thc.release_cached_memory()  # nothing kept: a no-op
+    # a further context works
+    out, *_ = _solve(thc, N, args)
+    assert all(np.isfinite(x.cpu().numpy()).all() for x in out)
+    thc.release_cached_memory()
+
+
+@pytest.mark.parametrize("kw", [{}, {"precision": 1}, {"flags": 8}], ids=["fp64", "mixed", "quintic"])
+def test_reused_memory_gives_the_same_bits_in_a_solve(thc, kw):
+    """Set-up, residual, density and a whole solve (DIIS buffers, inner products) on memory of the library's that
+    was just handed out, on that of the context before, and on a workspace of NaNs: the same bits."""
+    import torch
+    gc.collect()
+    args = _inputs(*N)
+    thc.release_cached_memory()
+    first, need, inside, after = _solve(thc, N, args, **kw)
+    assert after - inside < need / 2  # kept ...
+    again, _, inside2, after2 = _solve(thc, N, args, **kw)
+    assert abs(inside2 - inside) < need / 2 and after2 - inside2 < need / 2  # ... and used, with nothing added
+    assert all(torch.equal(a, b) for a, b in zip(first, again))
+    thc.release_cached_memory()
+    ws = torch.full(((need + 7) // 8,), float("nan"), dtype=torch.float64, device="cuda")
+    nans, *_ = _solve(thc, N, args, workspace=ws, **kw)
+    assert all(torch.equal(a, b) for a, b in zip(first, nans))
+
+
+def test_contexts_and_releases_on_several_threads(thc):
+    """Contexts opened and closed on three streams by three threads while a fourth keeps releasing: no result changes."""
+    import torch
+    sizes = [(6, 20, 30, 40, 60), (6, 24, 40, 66, 80), (5, 30, 70, 50, 90)]
+    inputs = [_inputs(*n) for n in sizes]
+    torch.cuda.synchronize()
+
+    def one(n, args):
+        ctx = thc.THC(*n)
+        Z = ctx.build_factors(*args)
+        out = [x.clone() for x in (Z, *ctx.residual(Z))]
+        torch.cuda.current_stream().synchronize()
+        ctx.close()
+        return out
+
+    want = [one(n, a) for n, a in zip(sizes, inputs)]
+    bad, done = [], threading.Event()
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(6):
+                if not all(torch.equal(a, b) for a, b in zip(want[k], one(sizes[k], inputs[k]))):
+                    bad.append(k)
+
+    def release():
+        while not done.wait(0.002):
+            thc.release_cached_memory()
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    r = threading.Thread(target=release)
+    r.start()
+    for x in ts:
+        x.start()
+    for x in ts:
+        x.join()
+    done.set()
+    r.join()
+    assert not bad
+    thc.release_cached_memory()
