@@ -276,7 +276,9 @@ int thc_get_state(thc_ctx* ctx, double* Z, double* t1);
 /* Replaces the state (t1 may be NULL = zero); clears the DIIS history. */
 int thc_set_state(thc_ctx* ctx, const double* Z, const double* t1);
 
-/* Device working memory held by the context (bytes), valid after thc_build_factors. */
+/* Device working memory held by the context (bytes), valid after thc_build_factors: its plan's bytes
+ * (thc_plan_info.device_bytes) or, where memory kept from a destroyed context was taken over, that
+ * block's length, at most twice them. */
 int thc_memory_bytes(const thc_ctx* ctx, size_t* bytes);
 
 /* How the context evaluates a residual, valid after thc_build_factors: the blocking of the

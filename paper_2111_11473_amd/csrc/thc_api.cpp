@@ -2416,7 +2416,7 @@ int thc_history(const thc_ctx* ctx, int max, double* energy, double* rnorm, doub
 
 int thc_memory_bytes(const thc_ctx* ctx, size_t* bytes) {
   if (!ctx || !bytes) return THC_EINVAL;
-  *bytes = ctx->bytes;
+  *bytes = std::max(ctx->bytes, ctx->arena_bytes);  // an arena taken over from another context may be longer than the plan
   return THC_OK;
 }
 

@@ -91,6 +91,31 @@ def test_reused_memory_gives_the_same_bits_in_a_solve(thc, kw):
     assert all(torch.equal(a, b) for a, b in zip(first, nans))
 
 
+def test_a_context_reports_the_memory_it_took_over(thc):
+    """A context on the longer arena of another one holds all of it and says so; its plan is its own."""
+    gc.collect()
+    small = (*N[:3], 120, 200)  # a shorter plan, longer than half of the other's
+    big_args, small_args = _inputs(*N), _inputs(*small)
+    thc.release_cached_memory()
+    big = thc.THC(*N)
+    big.build_factors(*big_args)
+    need = big.memory_bytes()
+    assert need == big.plan()["device_bytes"]
+    big.close()
+    ctx = thc.THC(*small)
+    ctx.build_factors(*small_args)
+    plan = ctx.plan()["device_bytes"]
+    assert need / 2 <= plan < need
+    assert ctx.memory_bytes() == need
+    ctx.close()
+    thc.release_cached_memory()
+    ctx = thc.THC(*small)
+    ctx.build_factors(*small_args)
+    assert ctx.memory_bytes() == ctx.plan()["device_bytes"] == plan
+    ctx.close()
+    thc.release_cached_memory()
+
+
 def test_contexts_and_releases_on_several_threads(thc):
     """Contexts opened and closed on three streams by three threads while a fourth keeps releasing: no result changes."""
     import torch
