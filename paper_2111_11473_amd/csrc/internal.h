@@ -197,8 +197,8 @@ hipError_t mlp_adam(int64_t n, float* p, const float* g, float* m, float* v, flo
 hipError_t mlp_init(int64_t n_in, int64_t w, int64_t n_out, uint64_t seed, float* p, hipStream_t s);
 // One training step of a network that mlp_infer_supported accepts: loss and gradient g of the mean
 // squared error on normalized targets and, for lr > 0, the Adam step on p, m, v.  H1, D2: rows x 256
-// floats; part: mlp_train_floats floats; lpart: one double per workgroup (at most 512).
-int64_t mlp_train_floats(int64_t n_in, int64_t n_out);
+// floats; part: mlp_train_floats of rows or of more rows; lpart: one double per workgroup (at most 512).
+int64_t mlp_train_floats(int64_t rows, int64_t n_in, int64_t n_out);
 hipError_t mlp_train(int64_t rows, int64_t n_in, int64_t n_out, const float* X, const float* T, const float* mu_in,
                      const float* sd_in, const float* mu_out, const float* sd_out, float* p, float* H1, float* D2,
                      float* part, double* lpart, float* loss, float* g, float* m, float* v, float lr, float b1,

@@ -815,8 +815,15 @@ hipError_t mlp_infer_bf16(int64_t rows, int64_t n_in, int64_t n_out, const float
   return hipGetLastError();
 }
 
-int64_t mlp_train_floats(int64_t n_in, int64_t n_out) {
-  return TRAIN_WGS * ((n_in + 2) * IW + (IW + 1) * n_out) + TRAIN_RANGES * IW * IW;
+// Workgroups of train_rows, row ranges of dW2 (256 rows, 16 MFMA steps a wave, or more each) and the length
+// of the workgroups' partials (the ranges' start 16 bytes aligned behind them).
+static int64_t train_wgs(int64_t rows) { return std::min<int64_t>((rows + TR - 1) / TR, TRAIN_WGS); }
+static int64_t train_ranges(int64_t rows) { return std::min<int64_t>((rows + 255) / 256, TRAIN_RANGES); }
+static int64_t train_part_floats(int64_t rows, int64_t n_in, int64_t n_out) {
+  return (train_wgs(rows) * ((n_in + 2) * IW + (IW + 1) * n_out) + 3) / 4 * 4;
+}
+int64_t mlp_train_floats(int64_t rows, int64_t n_in, int64_t n_out) {
+  return train_part_floats(rows, n_in, n_out) + train_ranges(rows) * IW * IW;
 }
 
 hipError_t mlp_train(int64_t rows, int64_t n_in, int64_t n_out, const float* X, const float* T, const float* mu_in,
@@ -824,11 +831,10 @@ hipError_t mlp_train(int64_t rows, int64_t n_in, int64_t n_out, const float* X, 
                      float* part, double* lpart, float* loss, float* g, float* m, float* v, float lr, float b1,
                      float b2, float eps, int64_t step, hipStream_t s) {
   if (rows < 1 || !mlp_infer_supported(n_in, IW, n_out)) return hipErrorInvalidValue;
-  const int nw = (int)std::min<int64_t>((rows + TR - 1) / TR, TRAIN_WGS);
-  // row ranges of dW2: 256 rows (16 MFMA steps a wave) or more each
-  const int64_t want = std::min<int64_t>((rows + 255) / 256, TRAIN_RANGES);
+  const int nw = (int)train_wgs(rows);
+  const int64_t want = train_ranges(rows);
   const int64_t per = ((rows + want - 1) / want + 15) / 16 * 16, ns = (rows + per - 1) / per;
-  float* part2 = part + TRAIN_WGS * ((n_in + 2) * IW + (IW + 1) * n_out);
+  float* part2 = part + train_part_floats(rows, n_in, n_out);
 #define ROWS(NO) hipLaunchKernelGGL(train_rows_kernel<NO>, dim3((unsigned)nw), dim3(TNT), 0, s, rows, (int)n_in, (int)n_out, X, T, mu_in, sd_in, mu_out, sd_out, p, H1, D2, part, lpart)
   if (n_out <= 2) ROWS(2); else ROWS(NOUT);
 #undef ROWS

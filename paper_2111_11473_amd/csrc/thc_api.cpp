@@ -1532,7 +1532,7 @@ struct thc_mlp {
         *d2 = nullptr, *d1 = nullptr;
   short* wb = nullptr;
   float* bb = nullptr;
-  float* tpart = nullptr;  // partial sums of the three-launch training step (allocated by its first call)
+  float* tpart = nullptr;  // partial sums of the three-launch training step, for `cap` rows
   bool packed = false;
   float* scratch = nullptr;            // device address of the allocation-free pass's scratch
   hipError_t scratch_err = hipSuccess;  // why it could not be looked up, if it could not
@@ -1559,12 +1559,16 @@ int mlp_reserve(thc_mlp* ctx, int64_t rows) {
   if (rows <= ctx->cap) return THC_OK;
   for (void* q : ctx->acts) (void)hipFree(q);
   ctx->acts.clear();
+  ctx->cap = 0;
   const int64_t R = std::max<int64_t>(rows, 1024), w = ctx->w;
   RCHK(mlp_alloc(ctx, &ctx->xn, (size_t)(R * ctx->n_in), ctx->acts));
   for (float** a : {&ctx->z1, &ctx->h1, &ctx->z2, &ctx->h2, &ctx->d2, &ctx->d1})
     RCHK(mlp_alloc(ctx, a, (size_t)(R * w), ctx->acts));
   RCHK(mlp_alloc(ctx, &ctx->yn, (size_t)(R * ctx->n_out), ctx->acts));
   RCHK(mlp_alloc(ctx, &ctx->dy, (size_t)(R * ctx->n_out), ctx->acts));
+  // here, not in the first training step, which may be under stream capture
+  if (mlp_infer_supported(ctx->n_in, ctx->w, ctx->n_out))
+    RCHK(mlp_alloc(ctx, &ctx->tpart, (size_t)mlp_train_floats(R, ctx->n_in, ctx->n_out), ctx->acts));
   ctx->cap = R;
   return THC_OK;
 }
@@ -1613,7 +1617,6 @@ int mlp_step(thc_mlp* ctx, const float* X, const float* T, int64_t R, float lr) 
   constexpr float B1 = 0.9f, B2 = 0.999f, EPS = 1e-8f;
   const int64_t step = ctx->step + 1;
   if (mlp_infer_supported(ctx->n_in, ctx->w, ctx->n_out)) {
-    if (!ctx->tpart) RCHK(mlp_alloc(ctx, &ctx->tpart, (size_t)mlp_train_floats(ctx->n_in, ctx->n_out), ctx->allocs));
     HIPCHK(mlp_train(R, ctx->n_in, ctx->n_out, X, T, ctx->mu_in, ctx->sd_in, ctx->mu_out, ctx->sd_out, ctx->p, ctx->h1,
                      ctx->d2, ctx->tpart, ctx->part, ctx->loss, ctx->g, ctx->m, ctx->v, lr, B1, B2, EPS, step,
                      ctx->stream));
