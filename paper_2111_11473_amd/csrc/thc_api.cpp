@@ -460,13 +460,18 @@ class RotationStream {
 };
 
 // Eigenvalues (ascending, host) and eigenvectors (columns of W) of the symmetric A (n x n, n >= EIG_DEV_MIN;
-// overwritten, like V and tab).  small: at least 64 n doubles; tab: at least 64 n.
+// overwritten, like V and tab).  small: at least 64 n doubles (tridiagonal, the reduction's scratch, n x 64
+// panels); tab: at least 64 n.
 constexpr int64_t EIG_DEV_MIN = 64;  // below, the host's eigensolver: the tables need a longer scratch and
                                      // a launch per column costs what the host takes for the whole problem
 
-int syev_device(thc_ctx* ctx, int64_t n, double* A, double* V, double* W, double* small, double* tab, int64_t tab_len,
-                std::vector<double>& w) {
+int syev_device(thc_ctx* ctx, int64_t n, double* A, double* V, double* W, double* small, int64_t small_len, double* tab,
+                int64_t tab_len, std::vector<double>& w) {
   hipStream_t s = ctx->stream;
+  if (small_len < std::max(2 * n + eig_tridiag_scratch(n), CB * n) || tab_len < CB * n) {
+    ctx->err = "eigensolver: scratch too short";
+    return THC_ENOMEM;
+  }
   double *dd = small, *de = small + n;
   MISC(eig_tridiag(n, A, V, dd, de, small + 2 * n, s));
   std::vector<double> de_h(2 * (size_t)n);
@@ -1927,7 +1932,8 @@ int thc_build_factors(thc_ctx* ctx, const double* L, const double* eps, const do
     std::vector<double> hw(P);
     MISC(eig_symmetrize(P, tmpw, Em, s));
     if (P >= EIG_DEV_MIN) {
-      rc = syev_device(ctx, P, Em, tP, ctx->W, tsolve, tmpw, std::max(Q, P) * std::max<int64_t>(std::max(nL, P), CB), hw);
+      rc = syev_device(ctx, P, Em, tP, ctx->W, tsolve, CB * std::max(std::max(nL, P), Q), tmpw,
+                       std::max(Q, P) * std::max<int64_t>(std::max(nL, P), CB), hw);
       if (rc) break;
     } else {
       std::vector<double> hC(PP);
