@@ -275,12 +275,13 @@ __global__ __launch_bounds__(256, OCC) void fgemm_kernel(const Gemm g, const int
 }
 
 // FP64 products on operands copied straight into LDS (no VGPR on the way): the kernel of every FP64
-// product with K > 64.
+// product.
 //
 // What bounds a large product here is the SIMD's register ports next to the matrix core: an FP64
 // MFMA takes 64 cycles, and everything that writes VGPRs beside it -- operand loads, LDS reads, the
 // scaling multiplies of a staged copy -- costs its issue and port cycles on top (the staged kernel
-// reached 62 TFLOP/s at 8192^3 where back-to-back MFMAs reach 72).  So a stage (8 k of a BM x BN
+// reached 62 TFLOP/s at 8192^3 where back-to-back MFMAs reach 68 to 78, by
+// the clock the card holds).  So a stage (8 k of a BM x BN
 // tile) goes to LDS by 16-byte buffer copies, NS stages deep, one barrier per stage, and is read as
 // 16-byte operands only: two k of a row (k-fastest operand) or two rows of one k (m- or n-fastest).
 //   k-fastest: LDS [row][4 granules of two k], granule g of row m at position g ^ (m / 4 % 4), so the
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, OCC) void dgemm_lds_kernel(const Ge
 // are O(2^-24) relative, the FP32 product's own rounding.  A thread loads packets of 4
 // consecutive k of one row, scales them, splits them and stores the three packets (8 bytes each)
 // to LDS, where a lane's MFMA fragment (row lr, k = 4 lk .. 4 lk + 3) is one packet.  One 16-k slab is one MFMA k-step; tiles, double
-// buffering, the XCD-aware order and the epilogue are those of the FP64/FP32 kernel.
+// buffering, the XCD-aware order and the epilogue are those of the FP32 kernel.
 typedef short bf4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 

@@ -1,6 +1,7 @@
-// Host FP64 dense linear algebra for small matrices (the DIIS overlap matrix, CP-ALS fallbacks,
-// working bases of rank below 64; larger set-up problems run on the device, eigen.hip):
-//  * Cholesky factorization and the inverse of a lower-triangular matrix;
+// Host FP64 dense linear algebra for small matrices (the DIIS overlap matrix, the learned guess's
+// target fits, working bases of rank below 64; larger set-up problems run on the device, eigen.hip):
+//  * Cholesky factorization, and the inverse of a lower-triangular matrix (which the host test of the
+//    factorization uses; the library's own inverses are the device's);
 //  * the symmetric eigenproblem: Householder reduction to tridiagonal form followed by the implicit
 //    QL iteration, with the orthogonal transformations accumulated (Golub & Van Loan, Matrix
 //    Computations, Sec. 8.3).

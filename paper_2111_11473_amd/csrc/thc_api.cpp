@@ -528,10 +528,10 @@ int check_finite_host(thc_ctx* ctx, const double* x, size_t n, const char* what)
 
 // ---------------------------------------------------------------------------------------
 // Working-memory plan.  Every device buffer of a context is a piece of one arena (one
-// allocation, or the caller's workspace): the persistent buffers (factors, state, DIIS, the
-// fused pass's block buffers, S and R of Alg. 7), the Alg. 6 region (the H block, its E, F, G
-// grid-point chunk and the C, D operands), which the set-up also uses as its scratch before the
-// first residual, and the chunk buffers of Alg. 7.  The plan picks the H block Xb (multiple of
+// allocation, or the caller's workspace): the persistent buffers (factors, state, DIIS, S and R of
+// Alg. 7), the Alg. 6 region (the H block, its E, F, G grid-point chunk and the C, D operands), which the
+// set-up also uses as its scratch before the first residual, the fused pass's block buffers (see
+// choose_plan), and the chunk buffers of Alg. 7.  The plan picks the H block Xb (multiple of
 // 64), the grid-point chunk Ic and the Alg. 7 row chunk X7 so the arena fits the budget: Ic near
 // 256 or more (each chunk reads and writes the H block once: H traffic per residual is
 // 16 P Pp^2 Q / Ic bytes, independent of Xb), then the largest Xb (each H block recomputes the
@@ -834,15 +834,15 @@ int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
   return THC_OK;
 }
 
-// The plan for the context's budget (its workspace, else the device's free memory up to
-// MEM_CAP), then the arena and every buffer in it.
-// The arena of the context destroyed last, kept for the next one.  A freed block is cleared by the
-// driver before it can be allocated again, at about 38 GB/s, so that programs that set up one system
-// after another wait for it in hipMalloc once all memory has been handed out: 161 ms for the 6.2 GB of
-// o = 20, where the whole set-up takes 13 ms.  At most one block is held, of at most ARENA_KEEP
-// bytes and 1/16 of the device's memory, and only while half of that memory is free; a context that
-// cannot use it (another device, longer, or shorter than half of it) returns it to the driver before it
-// allocates, and thc_release_cached_memory returns it at any time.  Blocks come in with their work finished and belong to nobody while they are here, so any
+// The arena of the context destroyed last, kept for the next one.  The driver clears freed memory, 28 ms
+// a GB (35 GB/s), and hipFree waits for it once a card's memory has been handed out before; programs that
+// set up one system after another then spend most of a set-up on it.  Set-ups in a row, by o (v = 9 o,
+// nL = 30 o, nP = 20 o, nQ = 50 o), with the arena kept / given back each time: 9 / 90 ms at o = 16
+// (3.0 GB), 13 / 173 at 20 (6.2), 15 / 221 at 22 (7.9); 286 at 24 (10.2), which is past the limit, 560 at 30.
+// At most one block is held, of at most ARENA_KEEP bytes and 1/16 of the device's memory, and only while
+// half of that memory is free; a context that cannot use it (another device, longer, or shorter than half
+// of it) returns it to the driver before it allocates, and thc_release_cached_memory returns it at any
+// time.  Blocks come in with their work finished and belong to nobody while they are here, so any
 // thread or stream may take one.
 struct ArenaBlock {
   void* p = nullptr;
@@ -896,6 +896,8 @@ hipError_t device_alloc(void** p, size_t bytes) {
   return e;
 }
 
+// The plan for the context's budget (its workspace, else the device's free memory up to
+// MEM_CAP), then the arena and every buffer in it.
 int plan_and_alloc(thc_ctx* ctx) {
   ctx->hslots = h_slots_per_xcd();
   if (ctx->hslots < 1) { ctx->err = "cannot query the device for the H-kernel launch"; return THC_EDEVICE; }
