@@ -816,7 +816,7 @@ int plan_with_block(thc_ctx* ctx, double budget, int64_t slots, int64_t nb) {
 // context the driver's clearing, 28 ms a GB (see ArenaBlock), so the plan grows by it only up to the
 // length of an arena that is kept for the next context; past that the blocks are cut until they fit the
 // memory of 64 vectors.  With memory of their own they cost 29% of a set-up at o = 22 (221 -> 286 ms, one
-// after another), 16% at o = 24, 6% at o = 30.
+// after another), 17% at o = 24, 6% at o = 30.
 int choose_plan(thc_ctx* ctx, double budget, int64_t slots) {
   const int64_t nL = ctx->nL, P = ctx->P, n2 = std::max(std::max(P, ctx->o), ctx->v);
   int64_t nb = ctx->opt.a_block > 0 ? ctx->opt.a_block : std::max<int64_t>(1, std::min<int64_t>(64, (int64_t)(4.0e9 / (32.0 * P * P))));
